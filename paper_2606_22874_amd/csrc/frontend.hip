@@ -37,18 +37,12 @@
 // lane of a group holds the same sum).
 #include <cmath>
 
-#include "spot_internal.h"
+#include "frontend_core.h"
 
 namespace spot {
 namespace {
 
 constexpr int kProjWaves = 4;
-constexpr int kMaxRopePairs = 64;
-
-// base^(-2i / rope_dim) for the rotary pairs i < rope_dim / 2 (FP64).
-struct RopeFreq {
-  double f[kMaxRopePairs];
-};
 
 // Sum over each aligned group of 16 lanes as the pairwise tree above; every
 // lane of the group ends with the group's sum.
@@ -193,16 +187,8 @@ __global__ __launch_bounds__(kProjWaves * 64) void project_kernel(
           pga[m] = src[dim_a];
           pgb[m] = src[dim_b];
         }
-        // 4. the rotation of the finishing lane's row: angle pos * freq in
-        // FP64, reduced to [-pi, pi] in FP64 (two-part 2 pi), sin and cos in
-        // FP32
-        if (rotate && wave == 0 && lane < nr) {
-          const double theta = (double)pos_l * freq.f[dim_a];
-          const double k = rint(theta * 0.15915494309189535);   // 1 / (2 pi)
-          double red = fma(-k, 6.283185307179586, theta);       // 2 pi, high part
-          red = fma(-k, 2.4492935982947064e-16, red);           // 2 pi, low part
-          sincosf((float)red, &s_rot, &c_rot);
-        }
+        // 4. the rotation of the finishing lane's row
+        if (rotate && wave == 0 && lane < nr) rope_sincos(pos_l, freq.f[dim_a], s_rot, c_rot);
       }
       // 5. the dot products of this pass
 #pragma unroll
@@ -314,21 +300,25 @@ __global__ __launch_bounds__(kProjWaves * 64) void project_kernel(
 }
 
 // One workgroup of 4 waves per (sequence, block to pool): block
-// j = first_block[b] + y.  Wave w sums tokens [16w, 16w + 16) of the block
+// j = first_block[b] + y, or with `pos` the block of position pos[b] (no
+// seq_len: tokens up to pos[b] count; a position outside the cache: nothing).  Wave w sums tokens [16w, 16w + 16) of the block
 // (all 16 rows in flight), lane l elements 8l .. 8l+7, as the pairwise tree;
 // the four partial sums are added in wave order, divided by the token count
 // and rounded to BF16.
 __global__ __launch_bounds__(256) void pool_kernel(const uint16_t* __restrict__ k_tok,
                                                    uint16_t* __restrict__ k_pool, int l_cap,
                                                    const int32_t* __restrict__ seq_len,
-                                                   const int32_t* __restrict__ first_block) {
+                                                   const int32_t* __restrict__ first_block,
+                                                   const int32_t* __restrict__ pos) {
   __shared__ float part[4][512];
   const int b = blockIdx.x;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int nblk = l_cap / kBlk;
-  int len = seq_len ? seq_len[b] : l_cap;
+  const int p = pos ? pos[b] : 0;
+  if (p < 0 || p >= l_cap) return;
+  int len = seq_len ? seq_len[b] : pos ? p + 1 : l_cap;
   len = len < 0 ? 0 : (len > l_cap ? l_cap : len);
-  const int j = (first_block ? first_block[b] : 0) + (int)blockIdx.y;
+  const int j = (first_block ? first_block[b] : p / kBlk) + (int)blockIdx.y;
   const int lo = j * kBlk, hi = min(lo + kBlk, len);
   if (j < 0 || j >= nblk || hi <= lo) return;
   const int n = hi - lo;
@@ -386,6 +376,17 @@ hipError_t launch_selector_project(const void* h, const void* w_q, const void* w
   const double lb = std::log2((double)rope_base);
   for (int i = 0; i < kMaxRopePairs; ++i)
     freq.f[i] = i < rope_dim / 2 ? std::exp2(-2.0 * i / rope_dim * lb) : 0.0;
+  if (project_mfma_takes(rows, d_model)) {
+    const ProjectArgs a{static_cast<const uint16_t*>(h), static_cast<const uint16_t*>(w_q),
+                        static_cast<const uint16_t*>(w_k), static_cast<const uint16_t*>(w_w), pos,
+                        rows, d_model, h_s, d_s, rope_dim, freq, static_cast<uint16_t*>(q_out),
+                        w_out, static_cast<uint16_t*>(k_cache), rows_per_seq, l_cap};
+    const hipError_t e = launch_project_mfma(a, s);
+    if (e != hipSuccess || !k_pool) return e;
+    hipLaunchKernelGGL(pool_kernel, dim3(rows), dim3(256), 0, s, a.k_cache,
+                       static_cast<uint16_t*>(k_pool), l_cap, seq_len, static_cast<const int32_t*>(nullptr), pos);
+    return hipGetLastError();
+  }
   const int rp = rows <= 4 ? 4 : (rows <= 8 ? 8 : 16);
   const int passes = (rows + rp - 1) / rp;
   // one row pass per workgroup row; more than 65535 passes take more launches
@@ -424,7 +425,7 @@ hipError_t launch_selector_pool(const void* k_tok, void* k_pool, int n_seq, int 
                                 int max_blocks, hipStream_t s) {
   hipLaunchKernelGGL(pool_kernel, dim3(n_seq, max_blocks), dim3(256), 0, s,
                      static_cast<const uint16_t*>(k_tok), static_cast<uint16_t*>(k_pool), l_cap,
-                     seq_len, first_block);
+                     seq_len, first_block, static_cast<const int32_t*>(nullptr));
   return hipGetLastError();
 }
 

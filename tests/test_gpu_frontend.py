@@ -109,6 +109,46 @@ def test_project_parity(rows, d_model, Hs, ds, rope_dim, base, rps, l_cap):
     assert np.all(cache_h[mask] == 0)
 
 
+# Rows at the edges of the kernel choice (row kernel, skinny tiles of 16 and
+# 32 tokens, 64 x 64, 128 x 64 and 256 x 128 tiles) and of their token tiles;
+# d_model below one step, ragged, and with more steps than buffers; every
+# rotary split (none, part, a partial group of 4, all).
+MANY_ROWS = [
+    # rows, d_model, Hs, ds, rope_dim, rows_per_seq, l_cap
+    (33, 4096, 4, 128, 64, 1, 8192),
+    (112, 1000, 8, 64, 32, 112, 128),
+    (113, 72, 8, 64, 64, 113, 128),
+    (225, 8, 4, 128, 0, 225, 256),
+    (320, 264, 4, 128, 128, 160, 192),
+    (2048, 328, 8, 64, 50, 1024, 1024),
+    (2049, 512, 4, 128, 64, 2049, 2112),
+    (4097, 136, 8, 64, 6, 4097, 4160),
+    (4352, 456, 4, 128, 64, 4352, 4352),
+]
+
+
+@pytest.mark.parametrize("rows,d_model,Hs,ds,rope_dim,rps,l_cap", MANY_ROWS)
+def test_project_many_rows_parity(rows, d_model, Hs, ds, rope_dim, rps, l_cap):
+    """The same bounds as test_project_parity; rows of one sequence in a
+    shuffled order, one position past the cache (no key stored)."""
+    print(f"[frontend] project rows={rows} d_model={d_model} {Hs}x{ds} rope {rope_dim}",
+          flush=True)
+    rng = np.random.default_rng(rows)
+    pos = np.concatenate([rng.permutation(l_cap)[:rps] for _ in range(rows // rps)])
+    pos[rows // 2] = l_cap
+    (h, wq, wk, ww), (q_out, w_out, cache), (q_o, k_o, w_o) = run_project(
+        rows, d_model, Hs, ds, rope_dim, 1.0e6, pos, rps, l_cap)
+    check_bf16(host_bf16(q_out), q_o, rot_sums(abs_sums(h, wq), Hs, ds, rope_dim))
+    cache_h = host_bf16(cache)
+    kept = np.flatnonzero(pos < l_cap)
+    k_g = np.stack([cache_h[r // rps, pos[r]] for r in kept])
+    check_bf16(k_g, k_o[kept], rot_sums(abs_sums(h, wk), Hs, ds, rope_dim)[kept])
+    assert np.all(np.abs(w_out.cpu().numpy() - w_o) <= 1e-5 * abs_sums(h, ww))
+    mask = np.ones(cache_h.shape[:2], bool)
+    mask[kept // rps, pos[kept]] = False
+    assert np.all(cache_h[mask] == 0)
+
+
 def test_project_skips_keys_outside_the_cache():
     rows, l_cap = 4, 128
     pos = np.array([5, -1, 128, 127], np.int32)
@@ -239,6 +279,45 @@ def test_fused_front_end_equals_project_then_pool(B, L, Hs, ds, rope_dim, with_l
             a, b = a.view(torch.int16), b.view(torch.int16)
         assert torch.equal(a, b), name
     assert not torch.equal(outs[1][3].view(torch.int16), pool0.view(torch.int16))
+
+
+@pytest.mark.parametrize("B,with_len", [(33, True), (41, False)])
+def test_pooled_front_end_of_many_sequences(B, with_len):
+    """More sequences than the one-launch kernel takes (projection on the
+    matrix cores, then one pooling launch): still bit for bit what
+    spot_selector_project and spot_selector_pool of each block give."""
+    L, Hs, ds, d_model = 256, 4, 128, 1024
+    rng = np.random.default_rng(B)
+    k_tok = bf16_bits(rng.standard_normal((B, L, Hs, ds), dtype=np.float32))
+    pos = rng.integers(0, L, B).astype(np.int32)
+    pos[:4] = [0, 63, 64, L]                                   # L: outside the cache
+    seq_len = np.minimum(pos + 1 + np.arange(B) % 3 * 9, L).astype(np.int32)
+    seq_len[3] = 0
+    h, wq, wk, ww = synth.selector_frontend(13, B, d_model, Hs, ds)
+    args = (bf(h), bf(wq), bf(wk), bf(ww), dev(pos))
+    outs = []
+    for fused in (False, True):
+        q_out = torch.empty((B, Hs, ds), dtype=torch.bfloat16, device=DEV)
+        w_out = torch.empty((B, Hs), dtype=torch.float32, device=DEV)
+        cache = bf(k_tok)
+        pooled = torch.zeros((B, L // 64, Hs, ds), dtype=torch.bfloat16, device=DEV)
+        sl = dev(seq_len) if with_len else None
+        if fused:
+            spot.spot_selector_project_pooled(*args, sl, B, d_model, Hs, ds, 64, 1.0e6, q_out,
+                                              w_out, cache, pooled, L)
+        else:
+            spot.spot_selector_project(*args, B, d_model, Hs, ds, 64, 1.0e6, q_out, w_out, cache,
+                                       1, L)
+            # (the sequence whose position is outside pools nothing)
+            spot.spot_selector_pool(cache, pooled, B, L, Hs, ds,
+                                    sl if with_len else dev(np.where(pos < L, pos + 1, 0)),
+                                    dev(pos // 64), 1)
+        outs.append((q_out, w_out, cache, pooled))
+    torch.cuda.synchronize()
+    for name, a, b in zip(("q_out", "w_out", "k_cache", "k_pool"), *outs):
+        if a.dtype == torch.bfloat16:
+            a, b = a.view(torch.int16), b.view(torch.int16)
+        assert torch.equal(a, b), name
 
 
 def test_front_end_in_a_graph_matches_eager():
