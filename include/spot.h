@@ -203,8 +203,8 @@ spot_status spot_selector_pool(const void *k_tok, void *k_pool, int n_seq, int l
  *  scores   device, float [rows, nblk]  (output)
  *
  * Supported: h_s * d_s == 512 with d_s in {64, 128}, any format and any
- * rows_per_seq (BF16 keys with rows_per_seq a multiple of 16 run on the
- * matrix cores, everything else on the vector units).
+ * rows_per_seq (calls with several rows per sequence and enough (row, key)
+ * pairs run on the matrix cores, everything else on the vector units).
  */
 spot_status spot_selector_score(const void *q_sel, const float *w, const void *k_sel,
                                 const void *k_scale, int kfmt, int n_seq, int rows_per_seq,
@@ -234,9 +234,9 @@ spot_status spot_selector_score(const void *q_sel, const float *w, const void *k
  * the matrix cores' block-scaled instruction (v_mfma_scale_f32_16x16x128_f8f6f4:
  * E2M1 or E4M3 operands, the E8M0 scales applied per 32-element group in
  * hardware).  Otherwise MX queries are decoded exactly in registers, and
- * integer queries enter the dot product as their integer codes, each lane's
- * partial sum (8 elements of one group) then multiplied by the group's
- * scale.  All paths accumulate in FP32.
+ * integer queries enter the dot product as their integer codes, each
+ * partial sum (8 elements of one group, or on the matrix cores all 32) then
+ * multiplied by the group's scale.  All paths accumulate in FP32.
  *
  * Errors: SPOT_ERR_NULL (a pointer, q_scale, or k_scale for quantized keys),
  * SPOT_ERR_SHAPE, SPOT_ERR_UNSUPPORTED (unknown query or key format, head
@@ -272,7 +272,8 @@ spot_status spot_selector_score_q(const void *q_sel, const void *q_scale, int qf
  *           [0, l_cap]); NULL means every token is visible
  *  scores   device, float [rows, nblk] (output)
  *
- * Supported: h_s * d_s == 512 with d_s in {64, 128}, any format.  Rows of one
+ * Supported: h_s * d_s == 512 with d_s in {64, 128}, any format.  Several rows
+ * over enough tokens (a prompt) run on the matrix cores; a few rows of one
  * sequence are scheduled on the same XCD so that they share its L2 for the
  * key stream.  Errors: SPOT_ERR_NULL for a missing pointer (or missing scales
  * of a 4-bit format), SPOT_ERR_SHAPE for negative sizes or l_cap not a

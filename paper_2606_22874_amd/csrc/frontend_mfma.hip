@@ -24,22 +24,14 @@
 #include <type_traits>
 
 #include "frontend_core.h"
+#include "mfma_core.h"
 
 namespace spot {
 namespace {
 
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-typedef float f32x2 __attribute__((ext_vector_type(2)));
-typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
-typedef __attribute__((address_space(3))) void lds_void;
+using namespace mc;
 
 constexpr int kOut = 512;        // h_s * d_s
-
-__device__ __forceinline__ f32x4 mfma(const u32x4& a, const u32x4& b, f32x4 c) {
-  return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a),
-                                                 __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
-}
 
 // First (B = false) or second dim of pair pp of a head.
 template <bool B>
@@ -53,10 +45,6 @@ template <bool B>
 __device__ __forceinline__ int pair_row(int P, int d_s, int rope) {
   const int sh = __builtin_ctz(d_s >> 1);
   return (P >> sh) * d_s + pair_dim<B>(P & ((d_s >> 1) - 1), d_s, rope);
-}
-
-__device__ __forceinline__ uint32_t pack2(float a, float b) {
-  return __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2{a, b}, bf16x2_t));
 }
 
 // Stores four values of pairs pp0 .. pp0+3's first (or second) dims.  With
@@ -106,17 +94,6 @@ __device__ __forceinline__ int swz(int r, int c) { return c ^ ((r >> 1) & 7); }
 
 __device__ __forceinline__ u32x4 frag(const unsigned char* t, int r, int c) {
   return *reinterpret_cast<const u32x4*>(t + r * kRowB + (swz(r, c) << 4));
-}
-
-// 16 bytes per lane, global -> LDS, lane l's at dst + 16 l.
-__device__ __forceinline__ void load_lds(const uint16_t* src, unsigned char* dst) {
-  __builtin_amdgcn_global_load_lds(src, (lds_void*)dst, 16, 0, 0);
-}
-
-// s_waitcnt: at most VM vector loads outstanding, every LDS access done.
-template <int VM>
-__device__ __forceinline__ void wait_loads() {
-  __builtin_amdgcn_s_waitcnt((VM & 15) | ((VM >> 4) << 14) | 0x0070);
 }
 
 // TT tokens x TD dims per workgroup of WT x WD waves.  S step buffers rotate:

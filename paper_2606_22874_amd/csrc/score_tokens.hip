@@ -4,8 +4,9 @@
 // tokens,
 //     sbar[r, b] = max_{t in b, t < seq_len[r]} sum_h w[r,h] ReLU(q[r,h,:] . k[seq(r), t, h, :]).
 //
-// The per-token cache is a streamed read (1 KiB per BF16 token), so the kernel
-// is bound by HBM and runs on the vector ALUs: with BF16 keys two wavefronts
+// For a few rows per sequence (decode; a prompt's many rows go to the matrix
+// cores, score_many.hip) the per-token cache is a streamed read (1 KiB per
+// BF16 token), so the kernel is bound by HBM and runs on the vector ALUs: with BF16 keys two wavefronts
 // share a 64-token block, 32 tokens each, and meet in LDS (quantized keys: one
 // wave per block); the loads are non-temporal (read
 // once, they should not evict anything).  Each lane reads the same 16 bytes
@@ -441,6 +442,9 @@ hipError_t launch_selector_score_tokens(const void* q_sel, const float* w, const
                                         const int32_t* seq_len, float* scores, hipStream_t s) {
   const int nblk = l_cap / kBlk;   // 64-token spans
   const int lph = d_s / 8;
+  if (score_many_takes(kfmt, n_seq, rows_per_seq, l_cap, true))
+    return launch_score_many(q_sel, nullptr, SPOT_KFMT_BF16, w, k_tok, k_scale, kfmt, n_seq,
+                             rows_per_seq, l_cap, d_s, blk, seq_len, scores, s);
   auto q = static_cast<const uint16_t*>(q_sel);
   auto k = static_cast<const uint8_t*>(k_tok);
   auto ks = static_cast<const uint8_t*>(k_scale);

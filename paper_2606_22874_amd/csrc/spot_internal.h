@@ -142,6 +142,15 @@ hipError_t launch_selector_score_tokens(const void* q_sel, const float* w, const
                                         int rows_per_seq, int l_cap, int blk, int d_s,
                                         const int32_t* seq_len, float* scores, hipStream_t s);
 
+// Many rows per sequence (score_many.hip): scores over pooled keys (sb = 1) or
+// the maxima over blocks of sb tokens; row r sees keys below see[r].  The
+// first says which calls it takes.
+bool score_many_takes(int kfmt, int n_seq, int rows_per_seq, int n_keys, bool tokens);
+hipError_t launch_score_many(const void* q, const void* q_scale, int qfmt, const float* w,
+                             const void* k, const void* k_scale, int kfmt, int n_seq,
+                             int rows_per_seq, int n_keys, int ds, int sb, const int32_t* see,
+                             float* scores, hipStream_t s);
+
 hipError_t launch_selector_project(const void* h, const void* w_q, const void* w_k,
                                    const void* w_w, const int32_t* pos, int rows, int d_model,
                                    int h_s, int d_s, int rope_dim, float rope_base, void* q_out,

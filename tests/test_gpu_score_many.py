@@ -1,0 +1,114 @@
+"""Parity of the matrix-core scorer of many query rows per sequence (a prompt)
+with the FP64 oracle (needs an MI355X): pooled keys, and per-token keys with
+blocks of 16 and 64 tokens, in every key and query format.
+
+Sizes lie at the edges of its tiles (64 rows and 32 keys per workgroup step,
+runs of several steps) and just past the number of (row, key) pairs that sends
+a call there; what each row sees is random: nothing, everything, past the end,
+and limits inside a tile.  Tolerance as for the row kernels:
+|gpu - oracle| <= 1e-4 |oracle| + 1e-6, the same -inf entries.
+"""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_2606_22874_amd import spot, synth
+from paper_2606_22874_amd.synth import bf16_bits
+
+pytestmark = [pytest.mark.gpu,
+              pytest.mark.skipif(not torch.cuda.is_available(), reason="needs a GPU")]
+
+DEV = "cuda:0"
+FORMATS = ("bf16", "int4", "mxfp4", "int8", "mxfp8")
+
+
+def dev(a):
+    return torch.from_numpy(np.ascontiguousarray(a)).to(DEV)
+
+
+def bf(a):
+    return spot.to_device_bf16(a, DEV)
+
+
+def assert_scores_close(g, o):
+    fin = np.isfinite(o)
+    assert np.array_equal(np.isfinite(g), fin)
+    assert np.all(g[~fin] == -np.inf)
+    err = np.abs(g[fin] - o[fin])
+    bound = 1e-4 * np.abs(o[fin]) + 1e-6
+    assert np.all(err <= bound), f"max excess {np.max(err - bound)}"
+
+
+def coded(x, fmt):
+    """(host codes, host scales, device codes, device scales) of BF16 bits x."""
+    if fmt == "bf16":
+        return x, None, bf(x), None
+    c, s = synth.QUANTIZERS[fmt](x)
+    s = s.view(np.uint16) if fmt in ("int4", "int8") else s
+    return c, s, dev(c), dev(s.view(np.int16) if fmt in ("int4", "int8") else s)
+
+
+def inputs(n_seq, rows, n_keys, Hs, ds):
+    rng = np.random.default_rng([n_seq, rows, n_keys, Hs])
+    q = bf16_bits(rng.standard_normal((n_seq * rows, Hs, ds), dtype=np.float32))
+    w = rng.uniform(0, 1, (n_seq * rows, Hs)).astype(np.float32)
+    k = bf16_bits(rng.standard_normal((n_seq, n_keys, Hs, ds), dtype=np.float32))
+    see = rng.integers(-3, n_keys + 40, n_seq * rows).astype(np.int32)
+    see[:3] = [0, n_keys, 1]
+    see[-rows // 2:] = np.minimum(see[-rows // 2:], n_keys // 3)   # some tiles see little
+    return q, w, k, see
+
+
+@pytest.mark.parametrize("n_seq,rows,n_keys,Hs,ds", [
+    (1, 64, 1025, 4, 128), (2, 65, 512, 8, 64), (1, 130, 799, 8, 64), (3, 129, 129, 4, 128),
+    (1, 1030, 63, 4, 128), (40, 17, 97, 8, 64)])
+@pytest.mark.parametrize("fmt", FORMATS)
+def test_pooled_keys(n_seq, rows, n_keys, Hs, ds, fmt):
+    print(f"[many] pooled {n_seq} x {rows} rows, {n_keys} keys, {Hs}x{ds} {fmt}", flush=True)
+    q, w, k, see = inputs(n_seq, rows, n_keys, Hs, ds)
+    kc, ks, kd, ksd = coded(k, fmt)
+    for lim in (see, None):
+        s_o = oracle.selector_score(q, w, kc, ks, fmt, rows_per_seq=rows, n_valid=lim,
+                                    nblk=n_keys, h_s=Hs, d_s=ds)
+        s_g = spot.selector_score(bf(q), dev(w), kd, ksd, fmt, rows_per_seq=rows,
+                                  n_valid=None if lim is None else dev(lim), nblk=n_keys)
+        assert_scores_close(s_g.cpu().numpy(), s_o)
+
+
+@pytest.mark.parametrize("qfmt", FORMATS[1:])
+@pytest.mark.parametrize("kfmt", FORMATS)
+def test_pooled_keys_quantized_queries(qfmt, kfmt):
+    print(f"[many] pooled q={qfmt} k={kfmt}", flush=True)
+    for n_seq, rows, n_keys, Hs, ds in ((1, 67, 799, 8, 64), (2, 66, 385, 4, 128)):
+        q, w, k, see = inputs(n_seq, rows, n_keys, Hs, ds)
+        qc, qs, qd, qsd = coded(q, qfmt)
+        kc, ks, kd, ksd = coded(k, kfmt)
+        s_o = oracle.selector_score_qk(qc, qs, qfmt, w, kc, ks, kfmt, n_seq * rows, n_keys, Hs,
+                                       ds, rows_per_seq=rows, n_valid=see)
+        out = torch.full((n_seq * rows, n_keys), 7.0, device=DEV)
+        spot.spot_selector_score_q(qd, qsd, qfmt, dev(w), kd, ksd, kfmt, n_seq, rows, n_keys, Hs,
+                                   ds, dev(see), out)
+        assert_scores_close(out.cpu().numpy(), s_o)
+
+
+@pytest.mark.parametrize("n_seq,rows,L,Hs,ds", [
+    (1, 96, 1024, 4, 128), (2, 65, 832, 8, 64), (3, 8, 4160, 4, 128), (1, 513, 448, 8, 64)])
+@pytest.mark.parametrize("fmt", FORMATS)
+def test_token_keys(n_seq, rows, L, Hs, ds, fmt):
+    """Both block sizes; the 64-token values are the largest of their four
+    16-token values, bit for bit."""
+    print(f"[many] tokens {n_seq} x {rows} rows, {L} tokens, {Hs}x{ds} {fmt}", flush=True)
+    q, w, k, see = inputs(n_seq, rows, L, Hs, ds)
+    kc, ks, kd, ksd = coded(k, fmt)
+    for lim in (see, None):
+        got = {}
+        for blk in (16, 64):
+            s_o = oracle.selector_score_tokens(q, w, kc, ks, fmt, rows_per_seq=rows, seq_len=lim,
+                                               l_cap=L, blk=blk, h_s=Hs, d_s=ds)
+            s_g = spot.selector_score_tokens(bf(q), dev(w), kd, ksd, fmt, rows_per_seq=rows,
+                                             seq_len=None if lim is None else dev(lim), l_cap=L,
+                                             blk=blk)
+            got[blk] = s_g.cpu().numpy()
+            assert_scores_close(got[blk], s_o)
+        assert np.array_equal(got[16].reshape(len(q), -1, 4).max(2), got[64])
