@@ -1,4 +1,5 @@
-"""Build libspot.so (gfx950) in-tree with hipcc.
+"""Build libspot.so (gfx950) in-tree with hipcc, and the Python binding's native
+marshalling (_binding.so, host code against torch's headers) with g++.
 
     python -m paper_2606_22874_amd.build
 
@@ -20,6 +21,7 @@ CSRC = os.path.join(PKG, "csrc")
 INCLUDE = os.path.join(ROOT, "include")
 BUILD = os.path.join(ROOT, "_build")
 SO = os.path.join(PKG, "libspot.so")
+BINDING = os.path.join(PKG, "_binding.so")
 ARCH = "gfx950"
 
 SOURCES = ["api.hip", "frontend.hip", "frontend_mfma.hip", "score.hip", "score_many.hip", "score_tokens.hip", "select.hip", "decode.hip", "step.hip", "prefill.hip",
@@ -59,10 +61,34 @@ def _compile(src: str) -> str:
     return obj
 
 
+def build_binding() -> str:
+    """The marshalling module (see csrc/binding.cpp)."""
+    import sysconfig
+
+    import torch
+    root = os.path.dirname(torch.__file__)
+    rocm = os.path.dirname(os.path.dirname(os.path.realpath(hipcc())))
+    tmp = BINDING + f".tmp{os.getpid()}"
+    cmd = [shutil.which("g++") or "g++", "-O2", "-std=c++17", "-fPIC", "-shared",
+           "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1", "-I", INCLUDE,
+           "-isystem", os.path.join(root, "include"), "-isystem", os.path.join(rocm, "include"),
+           "-isystem", sysconfig.get_paths()["include"], "-Wall",
+           os.path.join(CSRC, "binding.cpp"), "-o", tmp, "-L", os.path.join(root, "lib"),
+           "-ltorch_python", "-ltorch_cpu", "-ltorch", "-lc10", "-lc10_hip",
+           f"-Wl,-rpath,{os.path.join(root, 'lib')}"]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError(f"g++ failed for binding.cpp:\n{r.stderr}")
+    os.replace(tmp, BINDING)
+    return BINDING
+
+
 def build(verbose: bool = False) -> str:
     os.makedirs(BUILD, exist_ok=True)
-    with ThreadPoolExecutor(min(len(SOURCES), os.cpu_count() or 4)) as ex:
+    with ThreadPoolExecutor(min(len(SOURCES) + 1, os.cpu_count() or 4)) as ex:
+        binding = ex.submit(build_binding)
         objs = list(ex.map(_compile, SOURCES))
+        binding.result()
     tmp = SO + f".tmp{os.getpid()}"
     cmd = [hipcc(), f"--offload-arch={ARCH}", "-shared", "-fPIC", "-o", tmp, *objs]
     r = subprocess.run(cmd, capture_output=True, text=True)
@@ -75,9 +101,9 @@ def build(verbose: bool = False) -> str:
 
 
 def stale() -> bool:
-    if not os.path.exists(SO):
+    if not os.path.exists(SO) or not os.path.exists(BINDING):
         return True
-    t = os.path.getmtime(SO)
+    t = min(os.path.getmtime(SO), os.path.getmtime(BINDING))
     deps = [os.path.join(CSRC, f) for f in os.listdir(CSRC)] + [os.path.join(INCLUDE, "spot.h")]
     return any(os.path.getmtime(p) > t for p in deps)
 

@@ -6,6 +6,11 @@ pointers plus the current HIP stream.  Every step of the path runs in the HIP
 kernels of libspot.so; there is no fallback: if the library cannot be loaded
 on a machine with a GPU, the first call raises.
 
+The checks and the call itself run in a native module (csrc/binding.cpp) for
+plain arguments; whatever it does not take (it answers None and has enqueued
+nothing) goes through the Python checks below, which are the reference for
+what is accepted and for every error.
+
 Convenience wrappers without the ``spot_`` prefix allocate outputs with torch.
 """
 from __future__ import annotations
@@ -49,6 +54,7 @@ class SpotError(RuntimeError):
 
 _lock = threading.Lock()
 _lib = None
+_native = None     # csrc/binding.cpp, once the library is loaded
 
 
 def load(path: Optional[str] = None):
@@ -107,8 +113,24 @@ def load(path: Optional[str] = None):
                      "spot_decode_step_q", "spot_decode_step_static", "spot_decode_step_status"):
             getattr(L, name).restype = ctypes.c_int32
         if path is None:
+            _load_native(L)
             _lib = L
         return L
+
+
+def _load_native(L):
+    """Hands the library's entry points to the native marshalling module."""
+    global _native
+    if not os.path.exists(_build.BINDING):
+        _build.build_binding()
+    from . import _binding
+    order = (L.spot_selector_score, L.spot_selector_score_q, L.spot_selector_score_tokens_blk,
+             L.spot_selector_project, L.spot_selector_project_pooled, L.spot_selector_pool,
+             L.spot_select_blocks, L.spot_sparse_decode_blk, L.spot_dense_decode,
+             L.spot_sparse_prefill, L.spot_decode_step, L.spot_decode_step_q,
+             L.spot_decode_step_static)
+    _binding.init(tuple(ctypes.cast(f, ctypes.c_void_p).value for f in order), torch.cuda.Stream)
+    _native = _binding
 
 
 # ------------------------------------------------------------- marshalling
@@ -167,6 +189,11 @@ def _sel_cache(k, k_scale, f, n_keys, h_s, d_s, name, scale_name="k_scale"):
 # ------------------------------------------------------------- C ABI calls
 def spot_selector_score(q_sel, w, k_sel, k_scale, kfmt, n_seq, rows_per_seq, nblk, h_s, d_s,
                         n_valid, scores, stream=None):
+    if _native is not None:
+        st = _native.selector_score(q_sel, w, k_sel, k_scale, kfmt, n_seq, rows_per_seq, nblk,
+                                    h_s, d_s, n_valid, scores, stream)
+        if st is not None:
+            return _check("spot_selector_score", st)
     rows = n_seq * rows_per_seq
     f = KFMT[kfmt] if isinstance(kfmt, str) else int(kfmt)
     _dev(q_sel, "q_sel", BF16, rows * h_s * d_s)
@@ -182,6 +209,11 @@ def spot_selector_score(q_sel, w, k_sel, k_scale, kfmt, n_seq, rows_per_seq, nbl
 
 def spot_selector_score_q(q_sel, q_scale, qfmt, w, k_sel, k_scale, kfmt, n_seq, rows_per_seq,
                           nblk, h_s, d_s, n_valid, scores, stream=None):
+    if _native is not None:
+        st = _native.selector_score_q(q_sel, q_scale, qfmt, w, k_sel, k_scale, kfmt, n_seq,
+                                      rows_per_seq, nblk, h_s, d_s, n_valid, scores, stream)
+        if st is not None:
+            return _check("spot_selector_score_q", st)
     rows = n_seq * rows_per_seq
     qf = KFMT[qfmt] if isinstance(qfmt, str) else int(qfmt)
     f = KFMT[kfmt] if isinstance(kfmt, str) else int(kfmt)
@@ -211,6 +243,12 @@ def _tokens_args(q_sel, w, k_tok, k_scale, kfmt, n_seq, rows_per_seq, l_cap, blk
 
 def spot_selector_score_tokens(q_sel, w, k_tok, k_scale, kfmt, n_seq, rows_per_seq, l_cap, h_s,
                                d_s, seq_len, scores, stream=None):
+    if _native is not None:
+        st = _native.selector_score_tokens_blk(q_sel, w, k_tok, k_scale, kfmt, n_seq,
+                                               rows_per_seq, l_cap, BLK, h_s, d_s, seq_len,
+                                               scores, stream)
+        if st is not None:
+            return _check("spot_selector_score_tokens", st)
     f = _tokens_args(q_sel, w, k_tok, k_scale, kfmt, n_seq, rows_per_seq, l_cap, 64, h_s, d_s,
                      seq_len, scores)
     _check("spot_selector_score_tokens", load().spot_selector_score_tokens(
@@ -220,6 +258,12 @@ def spot_selector_score_tokens(q_sel, w, k_tok, k_scale, kfmt, n_seq, rows_per_s
 
 def spot_selector_score_tokens_blk(q_sel, w, k_tok, k_scale, kfmt, n_seq, rows_per_seq, l_cap,
                                    blk, h_s, d_s, seq_len, scores, stream=None):
+    if _native is not None:
+        st = _native.selector_score_tokens_blk(q_sel, w, k_tok, k_scale, kfmt, n_seq,
+                                               rows_per_seq, l_cap, blk, h_s, d_s, seq_len,
+                                               scores, stream)
+        if st is not None:
+            return _check("spot_selector_score_tokens_blk", st)
     f = _tokens_args(q_sel, w, k_tok, k_scale, kfmt, n_seq, rows_per_seq, l_cap, blk, h_s, d_s,
                      seq_len, scores)
     _check("spot_selector_score_tokens_blk", load().spot_selector_score_tokens_blk(
@@ -229,6 +273,12 @@ def spot_selector_score_tokens_blk(q_sel, w, k_tok, k_scale, kfmt, n_seq, rows_p
 
 def spot_selector_project(h, w_q, w_k, w_w, pos, rows, d_model, h_s, d_s, rope_dim, rope_base,
                           q_out, w_out, k_cache, rows_per_seq, l_cap, stream=None):
+    if _native is not None:
+        st = _native.selector_project(h, w_q, w_k, w_w, pos, rows, d_model, h_s, d_s, rope_dim,
+                                      rope_base, q_out, w_out, k_cache, rows_per_seq, l_cap,
+                                      stream)
+        if st is not None:
+            return _check("spot_selector_project", st)
     n_out = h_s * d_s
     _dev(h, "h", BF16, rows * d_model)
     _dev(w_q, "w_q", BF16, n_out * d_model)
@@ -247,6 +297,12 @@ def spot_selector_project(h, w_q, w_k, w_w, pos, rows, d_model, h_s, d_s, rope_d
 def spot_selector_project_pooled(h, w_q, w_k, w_w, pos, seq_len, n_seq, d_model, h_s, d_s,
                                  rope_dim, rope_base, q_out, w_out, k_cache, k_pool, l_cap,
                                  stream=None):
+    if _native is not None:
+        st = _native.selector_project_pooled(h, w_q, w_k, w_w, pos, seq_len, n_seq, d_model, h_s,
+                                             d_s, rope_dim, rope_base, q_out, w_out, k_cache,
+                                             k_pool, l_cap, stream)
+        if st is not None:
+            return _check("spot_selector_project_pooled", st)
     n_out = h_s * d_s
     _dev(h, "h", BF16, n_seq * d_model)
     _dev(w_q, "w_q", BF16, n_out * d_model)
@@ -267,6 +323,11 @@ def spot_selector_project_pooled(h, w_q, w_k, w_w, pos, seq_len, n_seq, d_model,
 
 def spot_selector_pool(k_tok, k_pool, n_seq, l_cap, h_s, d_s, seq_len=None, first_block=None,
                        max_blocks=None, stream=None):
+    if _native is not None:
+        st = _native.selector_pool(k_tok, k_pool, n_seq, l_cap, h_s, d_s, seq_len, first_block,
+                                   max_blocks, stream)
+        if st is not None:
+            return _check("spot_selector_pool", st)
     _dev(k_tok, "k_tok", BF16, n_seq * l_cap * h_s * d_s)
     _dev(k_pool, "k_pool", BF16, n_seq * (l_cap // 64) * h_s * d_s)
     if seq_len is not None:
@@ -282,6 +343,11 @@ def spot_selector_pool(k_tok, k_pool, n_seq, l_cap, h_s, d_s, seq_len=None, firs
 
 def spot_select_blocks(scores, rows, nblk, n_valid, top_p, k_max, k_min, n_sink, n_recent, idx,
                        count, nuc_mass=None, stream=None):
+    if _native is not None:
+        st = _native.select_blocks(scores, rows, nblk, n_valid, top_p, k_max, k_min, n_sink,
+                                   n_recent, idx, count, nuc_mass, stream)
+        if st is not None:
+            return _check("spot_select_blocks", st)
     _dev(scores, "scores", F32, rows * nblk)
     if n_valid is not None:
         _dev(n_valid, "n_valid", I32, rows)
@@ -300,6 +366,11 @@ def spot_decode_workspace_bytes(batch, h_q, h_kv, d, max_blocks) -> int:
 
 def spot_sparse_decode(q, k, v, seq_len, idx, count, k_max, batch, h_q, h_kv, d, l_cap,
                        sm_scale, out, lse, ws, stream=None):
+    if _native is not None:
+        st = _native.sparse_decode_blk(q, k, v, seq_len, idx, count, k_max, BLK, batch, h_q, h_kv,
+                                       d, l_cap, sm_scale, out, lse, ws, stream)
+        if st is not None:
+            return _check("spot_sparse_decode", st)
     _decode_args(q, k, v, seq_len, idx, count, k_max, batch, h_q, h_kv, d, l_cap, out, lse, ws)
     _check("spot_sparse_decode", load().spot_sparse_decode(
         _ptr(q), _ptr(k), _ptr(v), _ptr(seq_len), _ptr(idx), _ptr(count), k_max, batch, h_q,
@@ -309,6 +380,11 @@ def spot_sparse_decode(q, k, v, seq_len, idx, count, k_max, batch, h_q, h_kv, d,
 
 def spot_sparse_decode_blk(q, k, v, seq_len, idx, count, k_max, blk, batch, h_q, h_kv, d, l_cap,
                            sm_scale, out, lse, ws, stream=None):
+    if _native is not None:
+        st = _native.sparse_decode_blk(q, k, v, seq_len, idx, count, k_max, blk, batch, h_q, h_kv,
+                                       d, l_cap, sm_scale, out, lse, ws, stream)
+        if st is not None:
+            return _check("spot_sparse_decode_blk", st)
     _decode_args(q, k, v, seq_len, idx, count, k_max, batch, h_q, h_kv, d, l_cap, out, lse, ws)
     _check("spot_sparse_decode_blk", load().spot_sparse_decode_blk(
         _ptr(q), _ptr(k), _ptr(v), _ptr(seq_len), _ptr(idx), _ptr(count), k_max, blk, batch,
@@ -331,6 +407,11 @@ def _decode_args(q, k, v, seq_len, idx, count, k_max, batch, h_q, h_kv, d, l_cap
 
 def spot_dense_decode(q, k, v, seq_len, batch, h_q, h_kv, d, l_cap, sm_scale, out, lse, ws,
                       stream=None):
+    if _native is not None:
+        st = _native.dense_decode(q, k, v, seq_len, batch, h_q, h_kv, d, l_cap, sm_scale, out,
+                                  lse, ws, stream)
+        if st is not None:
+            return _check("spot_dense_decode", st)
     _dev(q, "q", BF16, batch * h_q * d)
     _dev(k, "k", BF16, batch * h_kv * l_cap * d)
     _dev(v, "v", BF16, batch * h_kv * l_cap * d)
@@ -346,6 +427,11 @@ def spot_dense_decode(q, k, v, seq_len, batch, h_q, h_kv, d, l_cap, sm_scale, ou
 
 def spot_sparse_prefill(q, k, v, L, idx, count, k_max, batch, h_q, h_kv, d, sm_scale, out, lse,
                         stream=None):
+    if _native is not None:
+        st = _native.sparse_prefill(q, k, v, L, idx, count, k_max, batch, h_q, h_kv, d, sm_scale,
+                                    out, lse, stream)
+        if st is not None:
+            return _check("spot_sparse_prefill", st)
     nqb = L // BLK
     _dev(q, "q", BF16, batch * h_q * L * d)
     _dev(k, "k", BF16, batch * h_kv * L * d)
@@ -369,6 +455,14 @@ def spot_decode_step(q_sel, w, k_sel, k_scale, kfmt, h_s, d_s, n_valid, top_p, k
                      scores, idx, count, nuc_mass, out, lse, ws, stream=None, q_scale=None,
                      qfmt="bf16"):
     """spot_decode_step, or spot_decode_step_q when qfmt is not BF16."""
+    if _native is not None:
+        st = _native.decode_step(q_sel, w, k_sel, k_scale, kfmt, h_s, d_s, n_valid, top_p, k_max,
+                                 k_min, n_sink, n_recent, q, k, v, seq_len, batch, h_q, h_kv, d,
+                                 l_cap, sm_scale, scores, idx, count, nuc_mass, out, lse, ws,
+                                 stream, q_scale, qfmt)
+        if st is not None:
+            return _check("spot_decode_step" if qfmt in (0, "bf16") else "spot_decode_step_q",
+                          st)
     nblk = l_cap // BLK
     f = KFMT[kfmt] if isinstance(kfmt, str) else int(kfmt)
     qf = KFMT[qfmt] if isinstance(qfmt, str) else int(qfmt)
@@ -406,6 +500,13 @@ def spot_decode_step_static(q_sel, w, k_sel, k_scale, kfmt, h_s, d_s, n_valid, t
                             k_min, n_sink, n_recent, q, k, v, seq_len, batch, h_q, h_kv, d, l_cap,
                             sm_scale, scores, idx, count, nuc_mass, out, lse, stream=None):
     """spot_decode_step on the device's static scratch (no workspace argument)."""
+    if _native is not None:
+        st = _native.decode_step_static(q_sel, w, k_sel, k_scale, kfmt, h_s, d_s, n_valid, top_p,
+                                        k_max, k_min, n_sink, n_recent, q, k, v, seq_len, batch,
+                                        h_q, h_kv, d, l_cap, sm_scale, scores, idx, count,
+                                        nuc_mass, out, lse, stream)
+        if st is not None:
+            return _check("spot_decode_step_static", st)
     nblk = l_cap // BLK
     f = KFMT[kfmt] if isinstance(kfmt, str) else int(kfmt)
     _dev(q_sel, "q_sel", BF16, batch * h_s * d_s)
