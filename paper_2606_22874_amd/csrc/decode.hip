@@ -7,6 +7,8 @@ namespace {
 
 using namespace dec;
 
+constexpr int kCus = 256;   // compute units of the device
+
 // Grid: n_pairs * n_slot workgroups; workgroup i serves pair i / n_slot with
 // slot i % n_slot.  SB: tokens per selected block (64, or 16 for the paper's
 // selector block; sparse only).
@@ -27,24 +29,42 @@ __global__ __launch_bounds__(64 * kDecWaves, 2) void decode_split_kernel(
 
 }  // namespace
 
-// Workgroups per (sequence, KV head) pair: aim for ~2048 waves over the grid
-// (8 per CU, so the whole grid is resident at once; 4 waves per workgroup
-// whatever the group size), at least one, and at
-// least two list entries per workgroup (with blocks of 16 tokens: two
-// virtual blocks of four entries).  Never more than with per_virtual = 1, so
-// a workspace sized for 64-token blocks fits.
-#ifndef SPOT_DECODE_WAVE_TARGET
-#define SPOT_DECODE_WAVE_TARGET 2048
-#endif
+// Splits per (sequence, KV head) pair that a workspace is laid out for: 2048
+// waves over the grid, at least one, at least two list entries per workgroup
+// (with blocks of 16 tokens: two virtual blocks of four entries).  Never more
+// than with per_virtual = 1, so a workspace sized for 64-token blocks fits.
 int decode_num_splits(int batch, int h_kv, int max_blocks, int group, int per_virtual) {
   const int pairs = batch * h_kv;
   (void)group;
-  int n = (SPOT_DECODE_WAVE_TARGET / kDecWaves + pairs - 1) / pairs;
+  int n = (2 * kCus + pairs - 1) / pairs;
   const int by_len = ((max_blocks + per_virtual - 1) / per_virtual + 1) / 2;
   if (n > by_len) n = by_len;
   const int min_for_ids = (max_blocks + kMaxIds - 1) / kMaxIds;  // entries per WG <= kMaxIds
   if (n < min_for_ids) n = min_for_ids;
   return n < 1 ? 1 : n;
+}
+
+// Workgroups per pair that are launched, at most the layout's splits.  One
+// workgroup of 4 waves per CU streams best: its two stages in flight fill
+// the memory system, and a second one on the CU only competes with it; CUs
+// with unequal numbers of workgroups finish apart.  Measured, us for 16 / 12
+// / 8 / 4 workgroups per pair of 32 pairs x 128 blocks: 25.3 / 28.5 / 25.2 /
+// 28.8; for 11 / 8 / 5 of 48 pairs: 43.1 / 39.6 / 35.6; for 64 / 32 / 16 of 8
+// pairs: 17.4 / 13.2 / 13.0.  So: the number whose grid leaves the fewest
+// idle workgroup places over whole rounds of 256, a second round counted 3 %
+// worse (128 pairs x 96 blocks: 69.9 us in one round, 73.0 in two).
+int decode_grid_splits(int batch, int h_kv, int max_blocks, int group, int per_virtual) {
+  const long long pairs = (long long)batch * h_kv;
+  const int most = decode_num_splits(batch, h_kv, max_blocks, group, per_virtual);
+  const int min_for_ids = (max_blocks + kMaxIds - 1) / kMaxIds;
+  int n = most;
+  double best = 0.0;
+  for (int i = min_for_ids > 1 ? min_for_ids : 1; i <= most && i * pairs <= 4 * kCus; ++i) {
+    const long long rounds = (pairs * i + kCus - 1) / kCus;
+    const double used = (double)(pairs * i) / (double)(kCus * rounds) * (1.03 - 0.03 * rounds);
+    if (used > best) best = used, n = i;
+  }
+  return n;
 }
 
 // Workspace: partial o [B, h_q, n_slot, d], partial (m, l) [B, h_q, n_slot],
@@ -64,7 +84,7 @@ hipError_t launch_decode(bool dense, const void* q, const void* k, const void* v
   const int G = h_q / h_kv;
   const bool b16 = !dense && blk == 16;
   const int max_blocks = dense ? l_cap / kBlk : k_max;
-  const int n_slot = decode_num_splits(batch, h_kv, max_blocks, G, b16 ? 4 : 1);
+  const int n_slot = decode_grid_splits(batch, h_kv, max_blocks, G, b16 ? 4 : 1);
   // The workspace layout follows the 64-token split count (never smaller),
   // so the completion counters sit at the same place for either block size.
   const int n_lay = decode_num_splits(batch, h_kv, max_blocks, G, 1);

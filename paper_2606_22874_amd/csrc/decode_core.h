@@ -14,8 +14,8 @@
 // transposed so that the scores never leave the registers (the GQA group's
 // heads are the 16 columns of each tile, G of them real):
 //   S^T = K Q^T       4 v_mfma_f32_16x16x32_bf16: the wave's 16 K rows are
-//                     the A operand straight from global memory (16-byte
-//                     loads), Q^T the B operand held for the whole loop;
+//                     the A operand (by way of LDS, so that the loads stay
+//                     coalesced), Q^T the B operand held for the whole loop;
 //   online softmax    per head = per lane column: block maximum over the 4
 //                     rows a lane holds and the 4 lane groups (two lane
 //                     swaps), a lazy rescale (only when a maximum grows by
@@ -171,7 +171,7 @@ __device__ __forceinline__ void merge_head(const float* __restrict__ ws_o,
 
 // ---------------------------------------------------------- LDS layout
 constexpr int kDecWaves = 4;         // waves per workgroup (16 token rows each)
-constexpr int kVRowBytes = kD * 2;   // one V row, 256 bytes
+constexpr int kRowBytes = kD * 2;    // one K or V row, 256 bytes
 constexpr float kLazy = 8.f;         // rescale only when a maximum grows by more (log2)
 
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
@@ -188,7 +188,8 @@ struct DecodeSmem {
     alignas(16) float o[kDecWaves][G][kD];            // [wave][head][dim]
   };
   union {
-    alignas(16) unsigned char v[kDecWaves][16 * kVRowBytes];   // each wave's V rows
+    // each wave's V rows, then its K rows
+    alignas(16) unsigned char kv[kDecWaves][2 * 16 * kRowBytes];
     Merge merge;
   };
   int ids[kMaxIds];
@@ -224,10 +225,14 @@ struct ListFromIdx {
                                             int nb_valid) const {
     (void)g;
     const int lane = __lane_id();
-    const int n_entries = min(count[b], k_max);
     const int32_t* lst = idx + (size_t)b * k_max;
-    int cnt = 0;
-    for (int base = slot; base < n_entries; base += 64 * n_slot) {
+    // The first 64 entries are read before the count is known (entries of
+    // the list's k_max words): one trip to memory instead of two.
+    const int e0 = slot + lane * n_slot;
+    const int first = lst[min(e0, k_max - 1)];
+    const int n_entries = min(count[b], k_max);
+    int cnt = append_ids(ids, 0, e0 < n_entries ? first : -1, nb_valid);
+    for (int base = slot + 64 * n_slot; base < n_entries; base += 64 * n_slot) {
       const int e = base + lane * n_slot;
       cnt = append_ids(ids, cnt, e < n_entries ? lst[e] : -1, nb_valid);
     }
@@ -242,6 +247,8 @@ struct ListFromIdx {
 // groups; XOR with 2 (r % 8) moves the chunk pairs apart and keeps each
 // pair's two chunks adjacent.
 __device__ __forceinline__ int swz_v(int r, int c) { return c ^ ((r & 7) << 1); }
+// The same for K, whose fragment read takes one chunk of each of 16 rows.
+__device__ __forceinline__ int swz_k(int r, int c) { return c ^ (r & 15); }
 
 // Two floats -> packed BF16 pair, round to nearest even.
 __device__ __forceinline__ uint32_t pack_bf16x2(float a, float b) {
@@ -322,7 +329,8 @@ __device__ __forceinline__ Partials<G> attend_blocks(DecodeSmem<G>& sm, const Qu
   static_assert(SB == kBlk || SB == 16, "blocks of 64 or 16 tokens");
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int r16 = lane & 15, kg = lane >> 4;   // tile column / row, lane group
-  unsigned char* vs = sm.v[wave];
+  unsigned char* vs = sm.kv[wave];
+  unsigned char* ks = vs + 16 * kRowBytes;
 
   // First token of this wave's 16 rows in (virtual) block n; -1 for padding.
   auto base_tok = [&](int n) -> int {
@@ -333,15 +341,20 @@ __device__ __forceinline__ Partials<G> attend_blocks(DecodeSmem<G>& sm, const Qu
       return id < 0 ? -1 : id * SB;
     }
   };
-  // K rows in the A layout of 16x16x32 (row r16, dims 32 kc + 8 kg .. +8) and
-  // V rows lane-contiguously (load i: row 4i + kg, chunk r16).
+  // K and V rows lane-contiguously (load i: row 4i + kg, chunk r16).  K goes
+  // through LDS to the A layout of 16x16x32 (row r16, dims 32 kc + 8 kg ..
+  // +8): loaded in that layout, four consecutive lanes touch four lines and
+  // the CU's address unit takes four times as long (a CU then moved at most
+  // 29 GB/s where it now moves 39: 128 blocks x 4 sequences on half of the
+  // CUs 36.7 -> 29.1 us, on all 25.5 -> 25.1, dense decode of 4 x 131072
+  // tokens 330 -> 320).
   auto load = [&](u32x4 (&kr)[4], u32x4 (&vr)[4], int n) {
     const int tb = max(base_tok(n), 0);
-    const uint16_t* kp = kh + (size_t)(tb + r16) * kD + 8 * kg;
+    const uint16_t* kp = kh + (size_t)tb * kD + lane * 8;
     const uint16_t* vp = vh + (size_t)tb * kD + lane * 8;
 #pragma unroll
-    for (int kc = 0; kc < 4; ++kc)
-      kr[kc] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(kp + 32 * kc));
+    for (int i = 0; i < 4; ++i)
+      kr[i] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(kp + i * 512));
 #pragma unroll
     for (int i = 0; i < 4; ++i)
       vr[i] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(vp + i * 512));
@@ -353,20 +366,27 @@ __device__ __forceinline__ Partials<G> attend_blocks(DecodeSmem<G>& sm, const Qu
   for (int dt = 0; dt < 8; ++dt) o[dt] = f32x4_t{0.f, 0.f, 0.f, 0.f};
   float m_run = -INFINITY, l_lane = 0.f;
 
-  // V rows of the stage into the wave's LDS rows (swizzled), then S^T.
+  // K and V rows of the stage into the wave's LDS rows (swizzled), then S^T.
   auto front = [&](const u32x4 (&kr)[4], const u32x4 (&vr)[4]) -> f32x4_t {
     wave_lds_sync();  // this wave's reads of the previous rows are issued
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       const int r = 4 * i + kg;
-      *reinterpret_cast<u32x4*>(vs + r * kVRowBytes + (swz_v(r, r16) << 4)) = vr[i];
+      *reinterpret_cast<u32x4*>(ks + r * kRowBytes + (swz_k(r, r16) << 4)) = kr[i];
     }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int r = 4 * i + kg;
+      *reinterpret_cast<u32x4*>(vs + r * kRowBytes + (swz_v(r, r16) << 4)) = vr[i];
+    }
+    wave_lds_sync();
     f32x4_t s = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int kc = 0; kc < 4; ++kc)
-      s = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, kr[kc]), qf.q[kc],
-                                                  s, 0, 0, 0);
-    wave_lds_sync();
+      s = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+          __builtin_bit_cast(bf16x8_t, *reinterpret_cast<const u32x4*>(
+                                           ks + r16 * kRowBytes + (swz_k(r16, 4 * kc + kg) << 4))),
+          qf.q[kc], s, 0, 0, 0);
     return s;
   };
   // Softmax of the block's scores and O^T += V^T P^T.
@@ -398,7 +418,7 @@ __device__ __forceinline__ Partials<G> attend_blocks(DecodeSmem<G>& sm, const Qu
     // columns 16 dt + 4 (r16 % 4) .. +3 and receives column 16 dt + r16 of
     // rows 4 kg .. 4 kg + 3.
     const int vr_row = 4 * kg + (r16 >> 2);
-    const unsigned char* vrow = vs + vr_row * kVRowBytes + (r16 & 1) * 8;
+    const unsigned char* vrow = vs + vr_row * kRowBytes + (r16 & 1) * 8;
 #pragma unroll
     for (int dt = 0; dt < 8; ++dt) {
       const int c = 2 * dt + ((r16 & 3) >> 1);
