@@ -703,4 +703,83 @@ __device__ __forceinline__ void sel_write(int32_t* __restrict__ out, int32_t* __
   }
 }
 
+// ---------------------------------------------------------------------------
+// Selection of a row of at most 64 blocks by a 4-wave workgroup, lane = block
+// id in every wave.  Short rows spend their time in the barriers and LDS
+// trips of select_row_core (2.1 us for 64 blocks, and 0.6 us more until every
+// workgroup has its share of the list); here every wave holds the whole row
+// and forms maximum, Z and the decision itself, and only the ranking is
+// shared out: wave w compares every candidate with blocks 16w .. 16w+15 (how
+// many are better, and their mass), one barrier, and every wave adds the
+// four parts in order.  The rule is select_row_core's; the mass of the better
+// candidates is summed in id order.
+struct Sel64Smem {
+  int rk[kSelWG / 64][64];
+  float mb[kSelWG / 64][64];
+};
+struct Sel64 {
+  uint64_t fin;   // bit id: block id is in S (the same in every thread)
+  float mass;     // nucleus mass
+};
+__device__ __forceinline__ Sel64 select_row_64(Sel64Smem& sm, float v, int nv, float top_p,
+                                               int k_max, int k_min, int n_sink, int n_recent) {
+  constexpr float kLog2e = 1.4426950408889634f;
+  constexpr int NW = kSelWG / 64;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int sink_end = min(n_sink, nv);
+  const int rec_start = max(0, nv - n_recent);
+  const int n_reserved = sink_end + (nv - rec_start) - max(0, sink_end - rec_start);
+  const int n_res = nv - n_reserved;
+  const int cap = min(k_max - n_reserved, n_res);
+  SPOT_SEL_TS(0);
+  const bool cand = lane >= sink_end && lane < rec_start;
+  const uint64_t resv = __ballot(lane < nv && !cand);
+  const uint32_t key = cand ? order_key(v) : 0u;
+  const float M = order_key_inv(wave_max_u(key));
+  const float pe = cand ? __builtin_amdgcn_exp2f((v - M) * kLog2e) : 0.f;
+  const float Z = wave_sum(pe);
+  SPOT_SEL_TS(1);
+  SPOT_SEL_TS(2);
+  int rk = 0;
+  float mb = 0.f;
+#pragma unroll
+  for (int u = 0; u < 64 / NW; ++u) {
+    const int j = wave * (64 / NW) + u;
+    const uint32_t kj = __builtin_amdgcn_readlane(key, j);
+    const float pj = readlane_f(pe, j);
+    // equal scores: the lower id first (a candidate's key is at least 1)
+    const bool better = kj > key - (lane > j ? 1u : 0u) && key != 0u;
+    rk += better ? 1 : 0;
+    mb += better ? pj : 0.f;
+  }
+  sm.rk[wave][lane] = rk;
+  sm.mb[wave][lane] = mb;
+  __syncthreads();
+  rk = 0;
+  mb = 0.f;
+#pragma unroll
+  for (int w = 0; w < NW; ++w) {
+    rk += sm.rk[w][lane];
+    mb += sm.mb[w][lane];
+  }
+  const bool surv = key != 0u && rk < cap;
+  const float msum = wave_sum(surv ? pe : 0.f);
+  const float pz = top_p * Z;
+  int n;
+  if (cap <= 0) n = 0;
+  else if (top_p >= 1.f) n = cap;
+  else if (top_p <= 0.f) n = 0;
+  else if (msum < pz) n = cap;
+  else n = max(__popcll(__ballot(surv && mb < pz)), 1);
+  const bool all = cap > 0 && top_p > 0.f && (top_p >= 1.f || msum < pz);
+  if (n_reserved + n < k_min) n = min(k_min - n_reserved, max(cap, 0));
+  float mass = 0.f;
+  if (n > 0 && Z > 0.f) {
+    const uint64_t at = __ballot(surv && rk == n - 1);
+    mass = (all ? msum : readlane_f(mb + pe, at ? __builtin_ctzll(at) : 0)) / Z;
+  }
+  SPOT_SEL_TS(4);
+  return Sel64{resv | __ballot(surv && rk < n), mass};
+}
+
 }  // namespace spot

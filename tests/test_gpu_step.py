@@ -10,6 +10,7 @@ exemptions of selcheck, and the outputs against the oracle run on the fused
 path's own block sets.
 """
 import copy
+import dataclasses
 
 import numpy as np
 import pytest
@@ -302,6 +303,46 @@ def test_step_short_rows(case, fmt):
     g = fus[4].float().cpu().numpy().astype(np.float64)
     assert np.max(np.abs(g - out_o)) <= 2e-2
     assert np.linalg.norm(g - out_o) / max(np.linalg.norm(out_o), 1e-30) <= 1e-2
+
+
+ROW64_RULES = [
+    Rule(0.9, 16, 0, 1, 2),         # the cap binds, or the nucleus ends before it
+    Rule(0.3, 64, 0, 1, 2),         # a nucleus of a few blocks
+    Rule(0.999, 64, 0, 0, 0),       # nearly everything, no reserved blocks
+    Rule(1.0, 7, 0, 0, 0),          # static top-K
+    Rule(1.0, 200, 0, 1, 2),        # everything (a cap past the row)
+    Rule(0.0, 9, 8, 1, 1),          # the floor alone
+    Rule(0.5, 40, 30, 2, 3),        # the floor extends the nucleus
+    Rule(0.9, 5, 0, 2, 3),          # reserved blocks fill the cap
+]
+
+
+@pytest.mark.parametrize("L", [4096, 4032, 64, 1088])
+@pytest.mark.parametrize("ties", [False, True])
+def test_step_row64_selection(L, ties):
+    """Rows of at most 64 blocks are selected in registers, lane = block:
+    every rule on ragged rows (one block, only reserved blocks, all), with
+    and without equal scores, against the oracle's rule on the same scores
+    and against the separate calls."""
+    lens = (L, max(1, L - 130), 1, min(L, 200))
+    wl = workload(2, B=4, L=L, seq_len=lens)
+    x = inputs(wl, "bf16")
+    if ties:   # few distinct keys: many equal scores
+        k = x["k_sel"].reshape(4, L // 64, 8, 64)
+        x = dict(x, k_sel=k[:, torch.arange(L // 64, device=DEV) % 5].contiguous())
+    for rule in ROW64_RULES:
+        print(f"[step] row64 L={L} ties={ties} {rule}", flush=True)
+        w2 = dataclasses.replace(wl, rule=rule)
+        sep, fus = separate(x, w2), fused(x, w2)
+        torch.cuda.synchronize()
+        s = fus[0].cpu().numpy()
+        i_o, c_o, m_o = oracle.select_blocks(s, rule, wl.n_valid)
+        i_g, c_g = fus[1].cpu().numpy(), fus[2].cpu().numpy()
+        check_all(s, wl.n_valid, rule, i_o, c_o, i_g, c_g)
+        same = np.all(i_g == i_o, axis=1)       # (a cut within rounding of p moves the mass)
+        assert np.allclose(fus[3].cpu().numpy()[same], m_o[same], rtol=1e-5, atol=1e-6)
+        if torch.equal(sep[1], fus[1]):
+            assert_same(sep, fus)
 
 
 def test_step_ragged_sequences():
