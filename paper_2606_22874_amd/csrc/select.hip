@@ -2,7 +2,8 @@
 // select-nucleus and select-topp) with a cap k_max on the set size.
 //
 // Three kernels, chosen by row length and cap (one row per workgroup):
-//  * rows of up to 512 blocks: one wavefront (select_wave_kernel);
+//  * rows of up to 512 blocks: one wavefront (select_wave_kernel), except
+//    where few rows or a static top-K make the next one faster;
 //  * 513 .. 8192 blocks: one 256-thread workgroup (select_wg_kernel, its body
 //    in select_core.h, shared with the fused decode step), for caps up to
 //    1024 and, when top_p >= 1 (static top-K: no survivor sort), any cap;
@@ -568,7 +569,10 @@ __global__ __launch_bounds__(64) void select_wave_kernel(
 }
 
 // Workgroup selection kernel: one 256-thread workgroup per row (rows of
-// 513 .. 8192 blocks, cap <= 512).
+// 513 .. 8192 blocks, cap <= 512; few rows of 65 .. 512 blocks).  Bound by its
+// chain of barriers and LDS trips, not by bytes: 4 waves share what
+// select_wave_kernel's one wave does in series (its radix passes and its
+// sort), 512 rows of 512 blocks 7.3 -> 6.0 us.
 template <int EPT, int SPL>
 __global__ __launch_bounds__(kSelWG) void select_wg_kernel(
     const float* __restrict__ scores, int nblk, const int32_t* __restrict__ n_valid,
@@ -590,6 +594,14 @@ __global__ __launch_bounds__(kSelWG) void select_wg_kernel(
   }
   int total;
   const int pos = sel_positions(sm, r.fin, total);
+  if constexpr (EPT <= 2) {
+    // Candidate scores with no finite maximum have no masses: NaN, as
+    // select_wave_kernel reports for rows of these sizes.
+    const float Z = (sm.red_f[0] + sm.red_f[1]) + (sm.red_f[2] + sm.red_f[3]);
+    const int sink_end = min(n_sink, nv), rec_start = max(0, nv - n_recent);
+    const int n_reserved = sink_end + (nv - rec_start) - max(0, sink_end - rec_start);
+    if (total > n_reserved && Z != Z) r.mass = Z;
+  }
   sel_write<EPT>(idx_out + (size_t)row * k_max, count_out + row,
                  mass_out ? mass_out + row : nullptr, k_max, r.fin, pos, total, r.mass);
 }
@@ -610,10 +622,23 @@ hipError_t launch_select_blocks(const float* scores, int rows, int nblk, const i
   // are never sorted and the survivor buffer (64 * SPL keys) does not bound
   // the cap: static top-K at any budget runs on the 512-key instantiation.
   const int spl_wg = top_p >= 1.f && spl > 8 ? 8 : spl;
-  if (nblk > 512 && nblk <= 8192 && spl_wg <= 16) {
-    const int e2 = nblk <= 1024 ? 4 : nblk <= 2048 ? 8 : nblk <= 4096 ? 16 : 32;
+  // Rows of 65 .. 512 blocks: four waves per row while the rows leave the
+  // chip's wave slots idle, one wave per row (less work in all) beyond that.
+  // us, one wave / four, replayed calls (rows x blocks, cap): 4 x 256, 32
+  // 5.6 / 4.8; 8 x 512, 64 6.9 / 5.3; 256 x 256, 64 5.9 / 5.4; 512 x 512, 64
+  // 7.3 / 6.0; 512 x 512, 96 8.2 / 7.6; 1024 x 256, 64 6.3 / 7.0; 2048 x 512,
+  // 64 8.8 / 10.8; 2048 x 512, 200 13.0 / 18.6.  Caps above 128, whose sort
+  // is one wave's either way, stay there too, as do rows of at most 64 blocks
+  // (64 rows: 5.1 / 5.1).  With top_p >= 1 only the one wave sorts: 512 x 300,
+  // 64 7.2 / 4.8; 2048 x 512, 512 18.0 / 5.9; so any cap goes (no survivor
+  // buffer), and large caps at any number of rows.
+  const bool short_row = nblk > 64 && nblk <= 512, top_k = top_p >= 1.f;
+  const bool short_wg = short_row && (rows <= 512 ? top_k || spl <= 2 : top_k && spl > 2);
+  const int spl_short = top_k ? 1 : spl;
+  if (short_wg || (nblk > 512 && nblk <= 8192 && spl_wg <= 16)) {
+    const int e2 = nblk <= 256 ? 1 : nblk <= 512 ? 2 : nblk <= 1024 ? 4 : nblk <= 2048 ? 8 : nblk <= 4096 ? 16 : 32;
 #define SPOT_SELECT_WG(E, S)                                                                    \
-    if (e2 == E && spl_wg == S) {                                                             \
+    if (e2 == E && (short_row ? spl_short : spl_wg) == S) {                               \
       hipLaunchKernelGGL((select_wg_kernel<E, S>), grid, dim3(kSelWG), 0, s, scores, nblk,    \
                          n_valid, top_p, k_max, k_min, n_sink, n_recent, idx, count,          \
                          nuc_mass);                                                           \
@@ -622,6 +647,8 @@ hipError_t launch_select_blocks(const float* scores, int rows, int nblk, const i
 #define SPOT_SELECT_WG_E(E)                                                      \
     SPOT_SELECT_WG(E, 1) SPOT_SELECT_WG(E, 2) SPOT_SELECT_WG(E, 4) SPOT_SELECT_WG(E, 8) \
     SPOT_SELECT_WG(E, 16)
+    SPOT_SELECT_WG(1, 1) SPOT_SELECT_WG(1, 2)
+    SPOT_SELECT_WG(2, 1) SPOT_SELECT_WG(2, 2)
     SPOT_SELECT_WG_E(4)
     SPOT_SELECT_WG_E(8)
     SPOT_SELECT_WG_E(16)

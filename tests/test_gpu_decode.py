@@ -201,6 +201,49 @@ def test_select_parity_same_scores(case):
     np.testing.assert_allclose(mass_g.cpu().numpy()[exact], mass_o[exact], atol=2e-5)
 
 
+@pytest.mark.parametrize("nblk", [64, 65, 128, 129, 255, 256, 257, 511, 512, 513])
+@pytest.mark.parametrize("rule", [
+    Rule(0.9, 32, 0, 1, 2),      # counted cut
+    Rule(0.8, 67, 0, 1, 2),      # cap 64: the last counted
+    Rule(0.99, 260, 20, 1, 2),   # sorted cut, or every candidate
+    Rule(1.0, 600, 0, 0, 0),     # cap above the row: everything
+    Rule(0.0, 16, 9, 2, 3),      # the k_min floor alone
+])
+def test_select_rows_around_kernel_sizes(nblk, rule):
+    """Rows at the edges between the selection kernels (64, 256 and 512
+    blocks) with ragged, empty and nearly empty rows among them.  The scores
+    are the same FP32 values on both sides, so only a row whose cumulative
+    mass sits within 1e-5 of p may differ."""
+    rows = 12
+    rng = np.random.default_rng(nblk)
+    nv = rng.integers(0, nblk + 1, rows).astype(np.int32)
+    nv[:4] = nblk, nblk - 1, 0, 1
+    s = synth.random_scores(500 + nblk, rows, nblk, nv)
+    idx_o, cnt_o, mass_o = oracle.select_blocks(s.astype(np.float64), rule, nv)
+    idx_g, cnt_g, mass_g = (x.cpu().numpy() for x in spot.select_blocks(f32(s), rule, i32(nv)))
+    stats = check_all(s, nv, rule, idx_o, cnt_o, idx_g, cnt_g, rel_tie=0.0)
+    assert stats["tie"] == 0 and stats["mass"] <= 1, stats
+    exact = cnt_g == cnt_o
+    np.testing.assert_allclose(mass_g[exact], mass_o[exact], atol=2e-5)
+
+
+@pytest.mark.parametrize("fill", [-np.inf, np.inf, np.nan, np.finfo(np.float32).min])
+@pytest.mark.parametrize("nblk,k_max", [(100, 32), (256, 100), (300, 32), (512, 100)])
+def test_select_short_rows_special_scores(nblk, k_max, fill):
+    """Infinite, NaN and lowest scores on rows of 65 .. 512 blocks: the few
+    rows of a small call and the many of a large one (which run different
+    kernels) get the same lists, and the same NaN masses."""
+    s = synth.random_scores(900 + nblk, 8, nblk, np.full(8, nblk, np.int32))
+    s[np.random.default_rng(nblk).random(s.shape) < 0.3] = fill
+    s[7] = fill
+    rule = Rule(0.9, k_max, 0, 1, 2)
+    few = [x.cpu().numpy() for x in spot.select_blocks(f32(s), rule)]
+    many = [x.cpu().numpy() for x in spot.select_blocks(f32(np.tile(s, (80, 1))), rule)]
+    np.testing.assert_array_equal(few[0], many[0][:8])
+    np.testing.assert_array_equal(few[1], many[1][:8])
+    np.testing.assert_allclose(few[2], many[2][:8], atol=2e-5)   # NaN equals NaN
+
+
 @pytest.mark.parametrize("rule", [Rule(0.9, 100, 0, 1, 2), Rule(0.02, 40, 0, 1, 2)])
 def test_select_deterministic_and_ties(rule):
     """Exact ties break toward the lower block id; repeated runs are bitwise
