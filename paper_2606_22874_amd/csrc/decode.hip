@@ -29,10 +29,19 @@ __global__ __launch_bounds__(64 * kDecWaves, 2) void decode_split_kernel(
 
 }  // namespace
 
-// Splits per (sequence, KV head) pair that a workspace is laid out for: 2048
-// waves over the grid, at least one, at least two list entries per workgroup
-// (with blocks of 16 tokens: two virtual blocks of four entries).  Never more
-// than with per_virtual = 1, so a workspace sized for 64-token blocks fits.
+// Workgroups per (sequence, KV head) pair: 2048 waves over the grid (two
+// workgroups of 4 waves per CU, all resident at once), at least one, at least
+// two list entries per workgroup (with blocks of 16 tokens: two virtual blocks
+// of four entries).  Never more than with per_virtual = 1, so a workspace
+// sized for 64-token blocks fits.
+// One workgroup per CU is enough where all sequences are of one length (us,
+// two / one per CU: dense, 4 x 65536 tokens 160 / 156, 6 x 49152 215 / 176; 128
+// blocks of 4 sequences 25.1 / 24.1), but the host does not know the
+// lengths, and a long sequence among short ones then has half the CUs: dense,
+// one of 65536 among 7 of 1024 86 / 155, half of 16 x 32768 165 / 184; 128
+// blocks of the one among 15 of 1024 33 / 51.  Fewer splits also leave fewer
+// rows whose largest P is exactly 1 before it is rounded to BF16 (error of
+// the output, 128 blocks x 4 sequences: 2.28e-3 / 2.31e-3).
 int decode_num_splits(int batch, int h_kv, int max_blocks, int group, int per_virtual) {
   const int pairs = batch * h_kv;
   (void)group;
@@ -42,29 +51,6 @@ int decode_num_splits(int batch, int h_kv, int max_blocks, int group, int per_vi
   const int min_for_ids = (max_blocks + kMaxIds - 1) / kMaxIds;  // entries per WG <= kMaxIds
   if (n < min_for_ids) n = min_for_ids;
   return n < 1 ? 1 : n;
-}
-
-// Workgroups per pair that are launched, at most the layout's splits.  One
-// workgroup of 4 waves per CU streams best: its two stages in flight fill
-// the memory system, and a second one on the CU only competes with it; CUs
-// with unequal numbers of workgroups finish apart.  Measured, us for 16 / 12
-// / 8 / 4 workgroups per pair of 32 pairs x 128 blocks: 25.3 / 28.5 / 25.2 /
-// 28.8; for 11 / 8 / 5 of 48 pairs: 43.1 / 39.6 / 35.6; for 64 / 32 / 16 of 8
-// pairs: 17.4 / 13.2 / 13.0.  So: the number whose grid leaves the fewest
-// idle workgroup places over whole rounds of 256, a second round counted 3 %
-// worse (128 pairs x 96 blocks: 69.9 us in one round, 73.0 in two).
-int decode_grid_splits(int batch, int h_kv, int max_blocks, int group, int per_virtual) {
-  const long long pairs = (long long)batch * h_kv;
-  const int most = decode_num_splits(batch, h_kv, max_blocks, group, per_virtual);
-  const int min_for_ids = (max_blocks + kMaxIds - 1) / kMaxIds;
-  int n = most;
-  double best = 0.0;
-  for (int i = min_for_ids > 1 ? min_for_ids : 1; i <= most && i * pairs <= 4 * kCus; ++i) {
-    const long long rounds = (pairs * i + kCus - 1) / kCus;
-    const double used = (double)(pairs * i) / (double)(kCus * rounds) * (1.03 - 0.03 * rounds);
-    if (used > best) best = used, n = i;
-  }
-  return n;
 }
 
 // Workspace: partial o [B, h_q, n_slot, d], partial (m, l) [B, h_q, n_slot],
@@ -84,7 +70,7 @@ hipError_t launch_decode(bool dense, const void* q, const void* k, const void* v
   const int G = h_q / h_kv;
   const bool b16 = !dense && blk == 16;
   const int max_blocks = dense ? l_cap / kBlk : k_max;
-  const int n_slot = decode_grid_splits(batch, h_kv, max_blocks, G, b16 ? 4 : 1);
+  const int n_slot = decode_num_splits(batch, h_kv, max_blocks, G, b16 ? 4 : 1);
   // The workspace layout follows the 64-token split count (never smaller),
   // so the completion counters sit at the same place for either block size.
   const int n_lay = decode_num_splits(batch, h_kv, max_blocks, G, 1);

@@ -344,10 +344,12 @@ __device__ __forceinline__ Partials<G> attend_blocks(DecodeSmem<G>& sm, const Qu
   // K and V rows lane-contiguously (load i: row 4i + kg, chunk r16).  K goes
   // through LDS to the A layout of 16x16x32 (row r16, dims 32 kc + 8 kg ..
   // +8): loaded in that layout, four consecutive lanes touch four lines and
-  // the CU's address unit takes four times as long (a CU then moved at most
-  // 29 GB/s where it now moves 39: 128 blocks x 4 sequences on half of the
-  // CUs 36.7 -> 29.1 us, on all 25.5 -> 25.1, dense decode of 4 x 131072
-  // tokens 330 -> 320).
+  // the CU's address unit takes four times as long.  That counts where few
+  // workgroups stream: us, loaded in that layout / through LDS, dense decode
+  // of one sequence of 65536 tokens among 7 of 1024 120 / 86, of 6 x 49152
+  // 235 / 215, 128 blocks x 4 sequences 26.8 / 25.1; with every CU streaming
+  // at the memory's rate the extra LDS trip costs 1-2 % (4 x 65536 159 / 160,
+  // half of 16 x 32768 160 / 164).
   auto load = [&](u32x4 (&kr)[4], u32x4 (&vr)[4], int n) {
     const int tb = max(base_tok(n), 0);
     const uint16_t* kp = kh + (size_t)tb * kD + lane * 8;

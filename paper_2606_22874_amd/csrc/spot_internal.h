@@ -165,11 +165,8 @@ hipError_t launch_select_blocks(const float* scores, int rows, int nblk, const i
                                 float top_p, int k_max, int k_min, int n_sink, int n_recent,
                                 int32_t* idx, int32_t* count, float* nuc_mass, hipStream_t s);
 
-// Splits a workspace is laid out for, and the workgroups per pair that a
-// launch uses (never more).  per_virtual: list entries per loop step (1; 4
-// for 16-token blocks)
+// per_virtual: list entries per loop step (1; 4 for 16-token blocks)
 int decode_num_splits(int batch, int h_kv, int max_blocks, int group, int per_virtual = 1);
-int decode_grid_splits(int batch, int h_kv, int max_blocks, int group, int per_virtual = 1);
 size_t decode_workspace_bytes(int batch, int h_q, int h_kv, int d, int max_blocks);
 
 // Byte offsets in a decode step's workspace: the control region [0, ctrl)

@@ -823,8 +823,7 @@ hipError_t launch_decode_step(const void* q_sel, const void* q_scale, int qfmt, 
   const StepWs L = static_ws ? step_static_layout(batch, h_q, h_kv, k_max)
                             : step_layout(batch, h_q, h_kv, k_max, 0);
   const int ns = decode_num_splits(batch, h_kv, k_max, h_q / h_kv);
-  const int ng = decode_grid_splits(batch, h_kv, k_max, h_q / h_kv);
-  const int n_slot_max = ng < kMaxSlots ? ng : kMaxSlots;
+  const int n_slot_max = ns < kMaxSlots ? ns : kMaxSlots;
   char* base = static_cast<char*>(ws);
   a.part_o = reinterpret_cast<float*>(base + L.part);
   a.part_ml = a.part_o + (size_t)batch * h_q * ns * kD;

@@ -403,6 +403,43 @@ def test_sparse_equals_dense_when_all_selected():
     assert torch.max(torch.abs(la - lb)).item() <= 1e-4
 
 
+@pytest.mark.parametrize("B,Hq,Hkv,blocks", [(8, 32, 8, 64), (6, 32, 8, 96), (4, 16, 8, 128),
+                                             (1, 8, 1, 1024), (130, 8, 8, 8), (3, 12, 4, 5)])
+def test_decode_runs_every_split(B, Hq, Hkv, blocks):
+    """A call writes the partials of every split its workspace is laid out for
+    (the host does not know the lengths: with fewer, a long sequence among short
+    ones has only a part of the chip), dense and sparse, 8 pairs to more than
+    there are workgroup places."""
+    d, lens = 128, np.full(B, 64, np.int32)
+    lens[0] = blocks * 64                        # one long sequence, the rest short
+    g = torch.Generator(device=DEV).manual_seed(B)
+    q = torch.randn((B, Hq, d), generator=g, device=DEV).bfloat16()
+    k, v = (torch.randn((B, Hkv, blocks * 64, d), generator=g, device=DEV).bfloat16()
+            for _ in range(2))
+    idx = torch.arange(blocks, dtype=torch.int32, device=DEV).repeat(B, 1)
+    cnt = i32((lens + 63) // 64)
+    words = B * Hq * (d + 2)
+    outs = []
+    for dense in (True, False):
+        ws = spot.decode_workspace(B, Hq, Hkv, d, blocks, DEV)
+        part = ws.view(torch.int32)
+        splits = (spot.spot_decode_workspace_bytes(B, Hq, Hkv, d, blocks) // 4 - B * Hkv) // words
+        assert splits * words + B * Hkv <= part.numel()
+        part[:splits * words] = 0x12345678       # (the counters after them stay zero)
+        out, lse = torch.empty_like(q), torch.empty((B, Hq), device=DEV)
+        if dense:
+            spot.spot_dense_decode(q, k, v, i32(lens), B, Hq, Hkv, d, blocks * 64, d ** -0.5, out,
+                                   lse, ws)
+        else:
+            spot.spot_sparse_decode(q, k, v, i32(lens), idx, cnt, blocks, B, Hq, Hkv, d,
+                                    blocks * 64, d ** -0.5, out, lse, ws)
+        torch.cuda.synchronize()
+        assert not torch.any(part[:splits * words] == 0x12345678), (dense, splits)
+        outs.append((out, lse))
+    assert torch.max(torch.abs(outs[0][0].float() - outs[1][0].float())).item() <= 2e-2
+    assert torch.max(torch.abs(outs[0][1] - outs[1][1])).item() <= 1e-4
+
+
 def test_full_step_deterministic():
     """Scores, selection and attention outputs are bitwise repeatable."""
     wl = workload(3)
