@@ -81,6 +81,14 @@ struct CompSum {
     e += (s - (t - y)) + (x - y);
     s = t;
   }
+  // (a sum that reached an infinity has none left to correct: its error terms
+  // are inf - inf)
+  __device__ __forceinline__ f32x4 value() const {
+    f32x4 r;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) r[i] = __builtin_isfinite(s[i]) ? s[i] + e[i] : s[i];
+    return r;
+  }
 };
 
 // ------------------------------------------------------------------ tiles
@@ -297,7 +305,7 @@ __global__ __launch_bounds__(64 * WT * WD) void proj_tile_kernel(ProjectArgs a, 
 
   // ---- w of this workgroup's token groups: lane holds heads 4 kg ..+3 of
   // token r16 of group wave / 4
-  s_w[wave][lane] = sw.s + sw.e;
+  s_w[wave][lane] = sw.value();
   __syncthreads();   // (also: every wave is done with the step buffers)
   if (wave % 4 == 0 && has_w) {
     const f32x4 s = (s_w[wave][lane] + s_w[wave + 1][lane]) +
@@ -439,7 +447,7 @@ __global__ __launch_bounds__(64 * kSkWaves) void proj_skinny_kernel(ProjectArgs 
   }
 #pragma unroll
   for (int t = 0; t < NT; ++t) {
-    part[wave][0][t][lane] = is_w ? sw[t].s + sw[t].e : acc[0][t];
+    part[wave][0][t][lane] = is_w ? sw[t].value() : acc[0][t];
     part[wave][1][t][lane] = acc[1][t];
   }
   __syncthreads();

@@ -149,6 +149,49 @@ def test_project_many_rows_parity(rows, d_model, Hs, ds, rope_dim, rps, l_cap):
     assert np.all(cache_h[mask] == 0)
 
 
+@pytest.mark.parametrize("rows", [40, 300])
+def test_project_many_rows_infinities(rows):
+    """Infinities, NaN and sums that overflow give what the row kernel gives
+    for the same rows 20 at a time (an infinite sum stays one: compensated sums
+    must not turn it into NaN), and every other row is untouched by them."""
+    d_model, Hs, ds, l_cap = 520, 4, 128, 320
+    h, wq, wk, ww = synth.selector_frontend(5, rows, d_model, Hs, ds)
+    ww = ww & 0x7FFF                                    # positive weights
+    inf, nan, big = 0x7F80, 0x7FC0, bf16_bits(np.float32(3.0e38)).item()
+    h[1, 7] = inf
+    h[2, :64] = big                                     # sums overflow in FP32
+    h[3, [9, 300]] = inf
+    h[4, 519] = inf ^ 0x8000
+    h[5, [2, 400]] = [inf, inf ^ 0x8000]                # inf - inf: NaN either way
+    h[rows - 1, 100] = nan
+    W = [bf(x) for x in (wq, wk, ww)]
+
+    def run(part, at):
+        n = len(part)
+        q_out = torch.empty((n, Hs * ds), dtype=torch.bfloat16, device=DEV)
+        w_out = torch.empty((n, Hs), dtype=torch.float32, device=DEV)
+        cache = torch.zeros((l_cap, Hs * ds), dtype=torch.bfloat16, device=DEV)
+        pos = dev(np.arange(at, at + n, dtype=np.int32))
+        spot.spot_selector_project(bf(part), *W, pos, n, d_model, Hs, ds, 64, 1.0e6, q_out, w_out,
+                                   cache, n, l_cap)
+        torch.cuda.synchronize()
+        return w_out, q_out, cache[at:at + n]
+
+    got = run(h, 0)
+    ref = [run(h[at:at + 20], at) for at in range(0, rows, 20)]
+    for i, (g, name) in enumerate(zip(got, ("w", "q", "k"))):
+        g = g.float().cpu().numpy()
+        r = np.concatenate([x[i].float().cpu().numpy() for x in ref])
+        if i:                    # q and k of the overflowing row depend on the order of the sum
+            g, r = np.delete(g, 2, 0), np.delete(r, 2, 0)
+        assert np.array_equal(np.isnan(g), np.isnan(r)), name
+        assert np.array_equal(np.isinf(g), np.isinf(r)), name
+        assert np.array_equal(np.sign(g[np.isinf(g)]), np.sign(r[np.isinf(r)])), name
+    w = got[0].cpu().numpy()
+    assert np.all(w[1:4] == np.inf) and np.all(w[4] == -np.inf) and np.all(np.isnan(w[5]))
+    assert np.all(np.isfinite(np.delete(w, [1, 2, 3, 4, 5, rows - 1], 0)))
+
+
 def test_project_skips_keys_outside_the_cache():
     rows, l_cap = 4, 128
     pos = np.array([5, -1, 128, 127], np.int32)
