@@ -233,8 +233,20 @@ __global__ __launch_bounds__(256) void score_many_kernel(ManyArgs a) {
   const int see_wg = max(max(s_see[0], s_see[1]), max(s_see[2], s_see[3]));
   const int kend = min(k1, see_wg);          // keys some row of the tile sees end here
 
-  // ---- scores of 32 keys against the wave's 16 rows
-  float m = -INFINITY;                       // SB == 64: the block's maximum so far
+  // A block's value: the largest of its visible scores that are no NaN.  Where
+  // all of them are NaN (w or a key infinite or NaN), v is, and the value is
+  // what the row kernels give: -inf from 4-bit keys, and for a 64-token block
+  // of BF16 keys of which at most half is visible (one of its two waves saw
+  // nothing); NaN otherwise.
+  auto put_block = [&](int j, float v) {
+    const bool low = C4 || (!KQ && SB == 64 && see <= j * SB + SB / 2);
+    if (kg == 0 && row_ok) out[j] = j * SB >= see ? -INFINITY : low ? fmaxf(v, -INFINITY) : v;
+  };
+
+  // ---- scores of 32 keys against the wave's 16 rows (unseen keys of a block: NaN,
+  // which no maximum takes)
+  constexpr float kUnseen = SB == 1 ? -INFINITY : __builtin_nanf("");
+  float m = kUnseen;                         // SB == 64: the block's maximum so far
   auto score = [&](const unsigned char* buf, const float* sc, int ks) {
 #pragma unroll
     for (int t = 0; t < kKeys / 16; ++t) {
@@ -280,7 +292,7 @@ __global__ __launch_bounds__(256) void score_many_kernel(ManyArgs a) {
       }
 #pragma unroll
       for (int i = 0; i < 4; ++i)
-        if (kt + 4 * kg + i >= see) acc[i] = -INFINITY;
+        if (kt + 4 * kg + i >= see) acc[i] = kUnseen;
       if constexpr (SB == 1) {
         if (row_ok) {
 #pragma unroll
@@ -291,12 +303,12 @@ __global__ __launch_bounds__(256) void score_many_kernel(ManyArgs a) {
         const float v = max_xor32(
             max_xor16(fmaxf(fmaxf(acc[0], acc[1]), fmaxf(acc[2], acc[3]))));
         if constexpr (SB == 16) {
-          if (kg == 0 && row_ok) out[kt / 16] = v;
+          put_block(kt / 16, v);
         } else {
           m = fmaxf(m, v);
           if (kt % 64 == 48) {
-            if (kg == 0 && row_ok) out[kt / 64] = m;
-            m = -INFINITY;
+            put_block(kt / 64, m);
+            m = kUnseen;
           }
         }
       }

@@ -112,3 +112,39 @@ def test_token_keys(n_seq, rows, L, Hs, ds, fmt):
             got[blk] = s_g.cpu().numpy()
             assert_scores_close(got[blk], s_o)
         assert np.array_equal(got[16].reshape(len(q), -1, 4).max(2), got[64])
+
+
+@pytest.mark.parametrize("blk", [16, 64])
+@pytest.mark.parametrize("fmt", FORMATS)
+def test_token_keys_special_values(fmt, blk):
+    """NaN and infinities in w and in BF16 keys: the same blocks are NaN, +inf
+    and -inf as from the row kernels, which take the same rows two at a time."""
+    rows, L, Hs, ds = 70, 2048, 4, 128
+    print(f"[many] special values {fmt} blocks of {blk}", flush=True)
+    q, w, k, _ = inputs(1, rows, L, Hs, ds)
+    w[3, 1] = np.nan
+    w[20:40, 2] = np.nan
+    w[40:50, 0] = np.inf
+    w[50:60, 3] = -np.inf
+    if fmt == "bf16":
+        k[0, 640:704, 1, 5] = 0x7FC0            # NaN keys: their head counts nothing
+        k[0, 700:900, 2, 9] = 0x7F80            # infinite ones
+    see = (L - 29 * np.arange(rows)).astype(np.int32)   # every rest of a block
+    see[[20, 21, 22, 23]] = [33, 32, 16, 1]
+    see[[40, 50]] = [0, 17]
+    _, _, kd, ksd = coded(k, fmt)
+
+    def run(at, n):
+        return spot.selector_score_tokens(bf(q[at:at + n]), dev(w[at:at + n]), kd, ksd, fmt,
+                                          rows_per_seq=n, seq_len=dev(see[at:at + n]), l_cap=L,
+                                          blk=blk).cpu().numpy()
+
+    many = run(0, rows)
+    few = np.concatenate([run(at, 2) for at in range(0, rows, 2)])
+    assert np.any(np.isnan(few)) or fmt in ("int4", "mxfp4")
+    assert np.any(few == np.inf) and np.any(few == -np.inf)
+    assert np.array_equal(np.isnan(many), np.isnan(few))
+    assert np.array_equal(np.isinf(many) * np.sign(many), np.isinf(few) * np.sign(few),
+                          equal_nan=True)
+    fin = np.isfinite(few)
+    assert np.all(np.abs(many[fin] - few[fin]) <= 1e-4 * np.abs(few[fin]) + 1e-6)
