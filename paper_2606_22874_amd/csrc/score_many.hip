@@ -266,12 +266,12 @@ __global__ __launch_bounds__(256) void score_many_kernel(ManyArgs a) {
             const int g = h * KS + x;
             const u32x4 kf = *reinterpret_cast<const u32x4*>(kr + swz(r16, g * 4 + kg) * 16);
             if constexpr (SCALED) {
+              // (one scale after the other: their product may overflow where
+              // the scaled sum does not)
               e[x] = mfma(kf, qf[g], f32x4{0.f, 0.f, 0.f, 0.f});
-              f32x4 f = {1.f, 1.f, 1.f, 1.f};
               if constexpr (KQ)
-                f = *reinterpret_cast<const f32x4*>(sc + g * kKeys + 16 * t + 4 * kg);
-              if constexpr (QINT) f *= qs[g];
-              e[x] *= f;
+                e[x] *= *reinterpret_cast<const f32x4*>(sc + g * kKeys + 16 * t + 4 * kg);
+              if constexpr (QINT) e[x] *= qs[g];
             } else {
               e[x] = mfma(kf, qf[g], x & 1 ? e[x - 1] : f32x4{0.f, 0.f, 0.f, 0.f});
             }

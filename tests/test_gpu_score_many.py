@@ -92,6 +92,35 @@ def test_pooled_keys_quantized_queries(qfmt, kfmt):
         assert_scores_close(out.cpu().numpy(), s_o)
 
 
+def test_pooled_keys_scales_beyond_their_product():
+    """Key and query scales whose product is no FP32 number while every scaled
+    sum is one: 2^117 and 2^-126 against FP16 query scales of 2048 and 2^-14."""
+    rows, n_keys, Hs, ds = 96, 1024, 4, 128
+    print("[many] pooled extreme scales", flush=True)
+    q = np.zeros((rows, Hs, ds), np.int8)
+    q[..., ::32] = 1
+    qs = np.full((rows, Hs, 4), 2048.0, np.float16)
+    qs[1::2] = 2.0 ** -14
+    kc = np.zeros((1, n_keys, Hs, ds), np.uint8)
+    kc[..., ::32] = 0x01                       # E4M3 2^-9
+    ks = np.full((1, n_keys, Hs, 4), 127 + 117, np.uint8)
+    kc[:, 1::2, :, ::32] = 0x78                # E4M3 2^8
+    ks[:, 1::2] = 127 - 126
+    w = np.ones((rows, Hs), np.float32)
+    got = []
+    for n in (rows, 4):                        # all rows, or four a call (the row kernel)
+        for at in range(0, rows, n):
+            out = torch.zeros((n, n_keys), device=DEV)
+            spot.spot_selector_score_q(dev(q[at:at + n]), dev(qs[at:at + n].view(np.int16)), "int8",
+                                       dev(w[at:at + n]), dev(kc), dev(ks), "mxfp8", 1, n, n_keys,
+                                       Hs, ds, None, out)
+            got.append(out.cpu().numpy())
+    want = 16 * np.where(np.arange(rows) % 2, 2.0 ** -14, 2048.0)[:, None] * \
+        np.where(np.arange(n_keys) % 2, 2.0 ** -118, 2.0 ** 108)
+    for g in (got[0], np.concatenate(got[1:])):
+        assert np.array_equal(g.astype(np.float64), want)
+
+
 @pytest.mark.parametrize("n_seq,rows,L,Hs,ds", [
     (1, 96, 1024, 4, 128), (2, 65, 832, 8, 64), (3, 8, 4160, 4, 128), (1, 513, 448, 8, 64)])
 @pytest.mark.parametrize("fmt", FORMATS)
