@@ -301,10 +301,12 @@ __global__ __launch_bounds__(kProjWaves * 64) void project_kernel(
 
 // One workgroup of 4 waves per (sequence, block to pool): block
 // j = first_block[b] + y, or with `pos` the block of position pos[b] (no
-// seq_len: tokens up to pos[b] count; a position outside the cache: nothing).  Wave w sums tokens [16w, 16w + 16) of the block
-// (all 16 rows in flight), lane l elements 8l .. 8l+7, as the pairwise tree;
-// the four partial sums are added in wave order, divided by the token count
-// and rounded to BF16.
+// seq_len: tokens up to pos[b] count; a position outside the cache: nothing).
+// Wave w sums tokens [16w, 16w + 16) of the block (all 16 rows in flight),
+// lane l elements 8l .. 8l+7, as the pairwise tree; the four partial sums are
+// added in wave order, divided by the token count and rounded to BF16.
+// WIDE: k_tok is 16-byte aligned; otherwise it is read 2 bytes at a time.
+template <bool WIDE>
 __global__ __launch_bounds__(256) void pool_kernel(const uint16_t* __restrict__ k_tok,
                                                    uint16_t* __restrict__ k_pool, int l_cap,
                                                    const int32_t* __restrict__ seq_len,
@@ -330,8 +332,16 @@ __global__ __launch_bounds__(256) void pool_kernel(const uint16_t* __restrict__ 
     const uint16_t* src = k_tok + ((size_t)b * l_cap + lo) * 512 + lane * 8;
     u32x4 x[16];
 #pragma unroll
-    for (int u = 0; u < 16; ++u)
-      x[u] = *reinterpret_cast<const u32x4*>(src + (size_t)min(t0 + u, n - 1) * 512);
+    for (int u = 0; u < 16; ++u) {
+      const uint16_t* at = src + (size_t)min(t0 + u, n - 1) * 512;
+      if constexpr (WIDE) {
+        x[u] = *reinterpret_cast<const u32x4*>(at);
+      } else {
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+          x[u][i] = (uint32_t)at[2 * i] | ((uint32_t)at[2 * i + 1] << 16);
+      }
+    }
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
       float t[16];
@@ -383,9 +393,15 @@ hipError_t launch_selector_project(const void* h, const void* w_q, const void* w
                         w_out, static_cast<uint16_t*>(k_cache), rows_per_seq, l_cap};
     const hipError_t e = launch_project_mfma(a, s);
     if (e != hipSuccess || !k_pool) return e;
-    hipLaunchKernelGGL(pool_kernel, dim3(rows), dim3(256), 0, s, a.k_cache,
-                       static_cast<uint16_t*>(k_pool), l_cap, seq_len, static_cast<const int32_t*>(nullptr), pos);
-    return hipGetLastError();
+    // (the cache's alignment is the caller's: this entry asks for none)
+    auto pool = [&](auto kern) {
+      hipLaunchKernelGGL(kern, dim3(rows), dim3(256), 0, s, a.k_cache,
+                         static_cast<uint16_t*>(k_pool), l_cap, seq_len,
+                         static_cast<const int32_t*>(nullptr), pos);
+      return hipGetLastError();
+    };
+    return (reinterpret_cast<uintptr_t>(k_cache) & 15u) == 0 ? pool(pool_kernel<true>)
+                                                             : pool(pool_kernel<false>);
   }
   const int rp = rows <= 4 ? 4 : (rows <= 8 ? 8 : 16);
   const int passes = (rows + rp - 1) / rp;
@@ -423,7 +439,7 @@ hipError_t launch_selector_project(const void* h, const void* w_q, const void* w
 hipError_t launch_selector_pool(const void* k_tok, void* k_pool, int n_seq, int l_cap,
                                 const int32_t* seq_len, const int32_t* first_block,
                                 int max_blocks, hipStream_t s) {
-  hipLaunchKernelGGL(pool_kernel, dim3(n_seq, max_blocks), dim3(256), 0, s,
+  hipLaunchKernelGGL(pool_kernel<true>, dim3(n_seq, max_blocks), dim3(256), 0, s,
                      static_cast<const uint16_t*>(k_tok), static_cast<uint16_t*>(k_pool), l_cap,
                      seq_len, first_block, static_cast<const int32_t*>(nullptr));
   return hipGetLastError();

@@ -363,6 +363,39 @@ def test_pooled_front_end_of_many_sequences(B, with_len):
         assert torch.equal(a, b), name
 
 
+@pytest.mark.parametrize("offset", [2, 8])
+def test_pooled_front_end_of_a_misaligned_cache(offset):
+    """The C entry asks for no alignment of k_cache (elements are BF16): a cache
+    that starts off a 16-byte boundary gives what an aligned one does, with more
+    sequences than the one-launch kernel takes as well."""
+    L, Hs, ds, d_model, n = 128, 4, 128, 512, 512
+    lib = spot.load()
+    for B in (20, 37):
+        rng = np.random.default_rng(B)
+        k_tok = bf16_bits(rng.standard_normal((B, L, Hs, ds), dtype=np.float32))
+        h, wq, wk, ww = (bf(x) for x in synth.selector_frontend(17, B, d_model, Hs, ds))
+        pos = dev(rng.integers(0, L, B).astype(np.int32))
+        outs = []
+        for off in (0, offset):
+            room = torch.zeros(B * L * n + 8, dtype=torch.bfloat16, device=DEV)
+            cache = room[off // 2:off // 2 + B * L * n]
+            assert cache.data_ptr() % 16 == off
+            cache.copy_(bf(k_tok).reshape(-1))
+            q_out = torch.zeros((B, n), dtype=torch.bfloat16, device=DEV)
+            w_out = torch.zeros((B, Hs), device=DEV)
+            pooled = torch.zeros((B, L // 64, n), dtype=torch.bfloat16, device=DEV)
+            torch.cuda.synchronize()
+            st = lib.spot_selector_project_pooled(
+                h.data_ptr(), wq.data_ptr(), wk.data_ptr(), ww.data_ptr(), pos.data_ptr(), None,
+                B, d_model, Hs, ds, 64, 1.0e6, q_out.data_ptr(), w_out.data_ptr(),
+                cache.data_ptr(), pooled.data_ptr(), L, torch.cuda.current_stream().cuda_stream)
+            assert st == spot.SPOT_OK
+            torch.cuda.synchronize()
+            outs.append((q_out, w_out, cache.clone(), pooled))
+        for a, b in zip(*outs):
+            assert torch.equal(a.view(torch.uint8), b.view(torch.uint8))
+
+
 def test_front_end_in_a_graph_matches_eager():
     """Projection and pooling captured in a HIP graph: every replay (with
     eager work and synchronisations between replays) gives the eager result."""
