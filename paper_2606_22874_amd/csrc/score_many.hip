@@ -376,8 +376,11 @@ hipError_t go_fmt(const ManyArgs& a, int ds, int sb, unsigned grid, hipStream_t 
 //     6.5 / 4.8 (there against 32 x 32 tiles straight from global memory)
 //   pooled keys, quantized: 64 x 512 4.6 / 5.9, 32 x 2048 6.8 / 5.8, 317 x 317
 //     9.1 / 5.6, 512 x 2048 75 / 8.4
-bool score_many_takes(int kfmt, int n_seq, int rows_per_seq, int n_keys, bool tokens) {
+bool score_many_takes(const void* k, int kfmt, int n_seq, int rows_per_seq, int n_keys,
+                      bool tokens) {
   const bool quant = kfmt != SPOT_KFMT_BF16;
+  // codes are read 16 bytes at a time here, 4 or 8 by the row kernels
+  if (quant && (reinterpret_cast<uintptr_t>(k) & 15u) != 0) return false;
   const long long pairs = (long long)n_seq * rows_per_seq * n_keys;
   const long long wgs = (long long)n_seq * ((rows_per_seq + kRows - 1) / kRows) *
                         ((n_keys + kKeys - 1) / kKeys);

@@ -177,3 +177,34 @@ def test_token_keys_special_values(fmt, blk):
                           equal_nan=True)
     fin = np.isfinite(few)
     assert np.all(np.abs(many[fin] - few[fin]) <= 1e-4 * np.abs(few[fin]) + 1e-6)
+
+
+@pytest.mark.parametrize("fmt,offset,tokens", [("int4", 4, False), ("mxfp4", 8, False),
+                                               ("int8", 8, False), ("mxfp8", 8, False),
+                                               ("int8", 8, True), ("mxfp8", 8, True)])
+def test_misaligned_codes(fmt, offset, tokens):
+    """The C entries take code caches aligned to what the row kernels read (4
+    bytes of 4-bit codes, 8 of 8-bit ones) in a call of any size."""
+    rows, n, Hs, ds = 128, 1024, 4, 128
+    print(f"[many] {fmt} codes {offset} bytes off, tokens {tokens}", flush=True)
+    q, w, k, see = inputs(1, rows, n, Hs, ds)
+    kc, ks, kd, ksd = coded(k, fmt)
+    room = torch.zeros(kd.numel() + 16, dtype=torch.uint8, device=DEV)
+    codes = room[offset:offset + kd.numel()]
+    codes.copy_(kd.reshape(-1).view(torch.uint8))
+    qd, wd, sd = bf(q), dev(w), dev(see)
+    out = torch.zeros((rows, n // 64 if tokens else n), device=DEV)
+    torch.cuda.synchronize()
+    lib, stream = spot.load(), torch.cuda.current_stream().cuda_stream
+    f = lib.spot_selector_score_tokens if tokens else lib.spot_selector_score
+    st = f(qd.data_ptr(), wd.data_ptr(), codes.data_ptr(), ksd.data_ptr(), spot.KFMT[fmt], 1, rows,
+           n, Hs, ds, sd.data_ptr(), out.data_ptr(), stream)
+    assert st == spot.SPOT_OK
+    torch.cuda.synchronize()
+    if tokens:
+        o = oracle.selector_score_tokens(q, w, kc, ks, fmt, rows_per_seq=rows, seq_len=see, l_cap=n,
+                                         blk=64, h_s=Hs, d_s=ds)
+    else:
+        o = oracle.selector_score(q, w, kc, ks, fmt, rows_per_seq=rows, n_valid=see, nblk=n,
+                                  h_s=Hs, d_s=ds)
+    assert_scores_close(out.cpu().numpy(), o)
