@@ -108,8 +108,11 @@ __device__ __forceinline__ float max_xor32(float x) {
 
 // SB: keys per output value (1: pooled keys; 16 or 64: tokens of a block).
 // QINT: INT4 / INT8 queries (a scale per row and group).
+// (Two workgroups per CU, as the LDS allows: left alone, the 8-bit kernels of
+// 128-dim heads take 258 registers and run one, 64 x 4 rows x 1024 keys 26 us
+// instead of 15.)
 template <int KFMT, int DS, int SB, bool QINT>
-__global__ __launch_bounds__(256) void score_many_kernel(ManyArgs a) {
+__global__ __launch_bounds__(256, 2) void score_many_kernel(ManyArgs a) {
   constexpr int HS = 512 / DS, KS = DS / 32;       // heads, groups per head
   constexpr bool KQ = KFMT != SPOT_KFMT_BF16;
   constexpr bool SCALED = KQ || QINT;
@@ -247,8 +250,11 @@ __global__ __launch_bounds__(256) void score_many_kernel(ManyArgs a) {
   // which no maximum takes)
   constexpr float kUnseen = SB == 1 ? -INFINITY : __builtin_nanf("");
   float m = kUnseen;                         // SB == 64: the block's maximum so far
+  // (with two scales a group the body twice is more than the compiler unrolls,
+  // and qf would go to scratch memory)
+  constexpr int kUnrollT = KQ && QINT && DS == 64 ? 1 : kKeys / 16;
   auto score = [&](const unsigned char* buf, const float* sc, int ks) {
-#pragma unroll
+#pragma unroll kUnrollT
     for (int t = 0; t < kKeys / 16; ++t) {
       const int kt = ks + 16 * t;            // the 16 keys' first
       if (kt >= k1) break;
