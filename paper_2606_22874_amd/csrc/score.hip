@@ -174,7 +174,7 @@ hipError_t launch_selector_score(const void* q_sel, const float* w, const void* 
                                  float* scores, hipStream_t s) {
   (void)h_s;
   const int rows = n_seq * rows_per_seq;
-  if (score_many_takes(k_sel, kfmt, n_seq, rows_per_seq, nblk, false))
+  if (score_many_takes(k_sel, kfmt, SPOT_KFMT_BF16, n_seq, rows_per_seq, nblk, false))
     return launch_score_many(q_sel, nullptr, SPOT_KFMT_BF16, w, k_sel, k_scale, kfmt, n_seq,
                              rows_per_seq, nblk, d_s, 1, n_valid, scores, s);
   dim3 grid(rows, (nblk + kBlocksPerWG - 1) / kBlocksPerWG);
@@ -221,7 +221,7 @@ hipError_t launch_selector_score_q(const void* q_sel, const void* q_scale, int q
                          qs, w, k, ks, rows, rows_per_seq, nblk, n_valid, scores);
     return hipGetLastError();
   }
-  if (score_many_takes(k_sel, kfmt, n_seq, rows_per_seq, nblk, false))
+  if (score_many_takes(k_sel, kfmt, qfmt, n_seq, rows_per_seq, nblk, false))
     return launch_score_many(q_sel, q_scale, qfmt, w, k_sel, k_scale, kfmt, n_seq, rows_per_seq,
                              nblk, d_s, 1, n_valid, scores, s);
   const dim3 grid(rows, (nblk + kBlocksPerWG - 1) / kBlocksPerWG);

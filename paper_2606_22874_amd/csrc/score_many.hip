@@ -370,30 +370,77 @@ hipError_t go_fmt(const ManyArgs& a, int ds, int sb, unsigned grid, hipStream_t 
 
 }  // namespace
 
+namespace {
+
+// How a call is split: row tiles, and runs of `steps` steps of keys per sequence.
+// As many steps per workgroup (at most 8) as leave two workgroups per CU (512)
+// in one round, at least one 64-token block (256 rows x 16384 tokens: 2 / 4 / 8
+// steps 12.9 / 10.4 / 13.9 us).
+struct Plan {
+  int row_tiles, runs, steps;
+  long long wgs;
+};
+Plan plan_of(int n_seq, int rows_per_seq, int n_keys, bool tokens) {
+  const int low = tokens ? 2 : 1, key_steps = (n_keys + kKeys - 1) / kKeys;
+  const int most = key_steps >= 8 ? 8 : (key_steps + low - 1) / low * low;
+  Plan p;
+  p.row_tiles = (rows_per_seq + kRows - 1) / kRows;
+  const long long tiles = (long long)n_seq * p.row_tiles, all = tiles * key_steps;
+  const long long steps = ((all + 511) / 512 + low - 1) / low * low;
+  p.steps = (int)(steps < low ? low : steps > most ? most : steps);
+  while (p.steps < most && tiles * ((key_steps + p.steps - 1) / p.steps) > 512) p.steps += low;
+  p.runs = (key_steps + p.steps - 1) / p.steps;
+  p.wgs = tiles * p.runs;
+  return p;
+}
+
+}  // namespace
+
 // The row kernels read every key once per row but start at once; here a call
 // costs two dependent trips to memory (queries, then keys) before its first
-// product.  Measured with replayed calls, the lines lie at these numbers of
-// (row, key) pairs; in us, row kernel / this one:
-//   token keys, BF16: 64 rows x 1024 keys 5.2 / 5.8, 8 x 8192 6.7 / 6.3,
-//     32 x 8192 15.6 / 6.4, 4 x 131072 43 / 28 (2 rows: 27.6 / 28.3)
-//   token keys, quantized: 64 x 1024 8.2 / 7.9, 8 x 8192 6.2 / 8.0, 12 x 8192
-//     8.6 / 8.0, 8 x 131072 44 / 28 (4 rows: 24 / 28)
-//   pooled keys, BF16: 4 x 2048 3.0 / 4.7, 8 x 2048 5.6 / 4.7, 512 x 512
-//     6.5 / 4.8 (there against 32 x 32 tiles straight from global memory)
-//   pooled keys, quantized: 64 x 512 4.6 / 5.9, 32 x 2048 6.8 / 5.8, 317 x 317
-//     9.1 / 5.6, 512 x 2048 75 / 8.4
-bool score_many_takes(const void* k, int kfmt, int n_seq, int rows_per_seq, int n_keys,
+// product, and a tile of 64 rows costs the same for two.
+//
+// Token keys: the lines lie at these numbers of (row, key) pairs; us, row kernel /
+// this one, replayed calls, (sequences x) rows x keys:
+//   BF16: 64 x 1024 5.1 / 5.7, 8 x 16 x 512 5.0 / 5.6, 64 x 1536 7.1 / 5.7; where
+//     the keys outgrow an XCD's L2 earlier: 8 x 8192 6.1 / 5.6, 8 x 4 x 2048
+//     6.9 / 6.1, 4 x 131072 43 / 24 (8 x 3 x 2048 7.0 / 6.0 stays)
+//   quantized: INT4 8 x 4 x 2048 5.7 / 7.7, 12 x 8192 8.3 / 7.7, 4 x 32768 8.6 /
+//     9.4, 8 x 131072 44 / 26; INT8 2 x 131072 22 / 25, 12 x 8192 11.3 / 7.5
+// Pooled keys: the smaller of two estimates, fitted to calls of 1 .. 1000
+// sequences, 2 .. 512 rows and 33 .. 20000 keys.
+//   This kernel: the steps of a workgroup, in rounds of 512 workgroups; integer and
+//   MX queries come in small pieces.  (BF16 200 x 200 5.2, 64 x 4 x 512 8.0, x 2048
+//   24.8; INT8 256 x 256 5.8, 64 x 4 x 512 9.1, x 2048 26.1; INT8 queries 9.6)
+//   Row kernel: pairs; BF16 keys once they outgrow an XCD's L2 (4 MB) twice as slow,
+//   but never below 32768 pairs.  (BF16 200 x 200 4.6, 8 x 5 x 1024 8.3, 64 x 4 x 2048
+//   76; INT8 222 x 222 6.0, 64 x 2 x 2048 22.2, 64 x 4 x 2048 40.5)
+bool score_many_takes(const void* k, int kfmt, int qfmt, int n_seq, int rows_per_seq, int n_keys,
                       bool tokens) {
   const bool quant = kfmt != SPOT_KFMT_BF16;
   // codes are read 16 bytes at a time here, 4 or 8 by the row kernels
   if (quant && (reinterpret_cast<uintptr_t>(k) & 15u) != 0) return false;
-  const long long pairs = (long long)n_seq * rows_per_seq * n_keys;
-  const long long wgs = (long long)n_seq * ((rows_per_seq + kRows - 1) / kRows) *
-                        ((n_keys + kKeys - 1) / kKeys);
-  if (wgs > 0x0fffffffLL) return false;      // grid size (padded to 8 runs a sequence)
+  const double pairs = (double)n_seq * rows_per_seq * n_keys;
+  const double keys = (double)n_seq * n_keys;
+  if (rows_per_seq < 2 || pairs <= 32768.) return false;
+  const Plan p = plan_of(n_seq, rows_per_seq, n_keys, tokens);
+  // grid size (padded to 8 runs): below 2^32 threads
+  if ((p.wgs / p.row_tiles + 7) / 8 * 8 * p.row_tiles > 0x00ffffffLL) return false;
   if (tokens)
-    return rows_per_seq >= (quant ? 8 : 4) && pairs >= (quant ? 98304 : 65536);
-  return rows_per_seq > 1 && pairs >= (quant ? 49152 : 16384);
+    return quant ? rows_per_seq >= 8 && pairs >= 98304.
+                 : rows_per_seq >= 4 && pairs >= (keys >= 8192. ? 65536. : 98304.);
+  const bool four_bit = kfmt == SPOT_KFMT_INT4_G32 || kfmt == SPOT_KFMT_MXFP4_G32;
+  const double rounds = (double)((p.wgs + 511) / 512);
+  double here = p.wgs <= 256 && p.steps == 1 ? (quant ? 5.7 : 5.1)
+                : rounds * (quant ? 3.8 + 3.0 * p.steps : 2.9 + 2.9 * p.steps);
+  if (qfmt == SPOT_KFMT_INT4_G32 || qfmt == SPOT_KFMT_INT8_G32)
+    here += 3.9;
+  else if (qfmt != SPOT_KFMT_BF16)
+    here += 2.3;
+  const double row = quant           ? 2.2 + (four_bit ? 6.4e-5 : 7.0e-5) * pairs
+                     : keys > 4096. ? 2.0 + 1.5e-4 * pairs
+                                    : 2.0 + 6.3e-5 * pairs;
+  return here < row;
 }
 
 hipError_t launch_score_many(const void* q, const void* q_scale, int qfmt, const float* w,
@@ -412,17 +459,11 @@ hipError_t launch_score_many(const void* q, const void* q_scale, int qfmt, const
   a.n_keys = n_keys;
   a.see = see;
   a.scores = scores;
-  a.row_tiles = (rows_per_seq + kRows - 1) / kRows;
-  // Steps per workgroup: as many as leave two workgroups per CU (512), at
-  // least one 64-token block, at most 8 (256 rows x 16384 tokens: 2 / 4 / 8
-  // steps 12.9 / 10.4 / 13.9 us).
-  const int low = sb == 1 ? 1 : 2;
-  const long long all = (long long)n_seq * a.row_tiles * ((n_keys + kKeys - 1) / kKeys);
-  long long steps = (all + 511) / 512;
-  steps = (steps + low - 1) / low * low;
-  a.steps = (int)(steps < low ? low : steps > 8 ? 8 : steps);
-  a.runs = (n_keys + a.steps * kKeys - 1) / (a.steps * kKeys);
-  const unsigned grid = (unsigned)(((long long)n_seq * a.runs + 7) / 8 * 8 * a.row_tiles);
+  const Plan p = plan_of(n_seq, rows_per_seq, n_keys, sb != 1);
+  a.row_tiles = p.row_tiles;
+  a.runs = p.runs;
+  a.steps = p.steps;
+  const unsigned grid = (unsigned)(((long long)n_seq * p.runs + 7) / 8 * 8 * p.row_tiles);
   switch (kfmt) {
     case SPOT_KFMT_BF16: return go_fmt<SPOT_KFMT_BF16>(a, ds, sb, grid, s);
     case SPOT_KFMT_INT4_G32: return go_fmt<SPOT_KFMT_INT4_G32>(a, ds, sb, grid, s);

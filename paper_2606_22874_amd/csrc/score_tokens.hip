@@ -442,7 +442,7 @@ hipError_t launch_selector_score_tokens(const void* q_sel, const float* w, const
                                         const int32_t* seq_len, float* scores, hipStream_t s) {
   const int nblk = l_cap / kBlk;   // 64-token spans
   const int lph = d_s / 8;
-  if (score_many_takes(k_tok, kfmt, n_seq, rows_per_seq, l_cap, true))
+  if (score_many_takes(k_tok, kfmt, SPOT_KFMT_BF16, n_seq, rows_per_seq, l_cap, true))
     return launch_score_many(q_sel, nullptr, SPOT_KFMT_BF16, w, k_tok, k_scale, kfmt, n_seq,
                              rows_per_seq, l_cap, d_s, blk, seq_len, scores, s);
   auto q = static_cast<const uint16_t*>(q_sel);

@@ -145,7 +145,7 @@ hipError_t launch_selector_score_tokens(const void* q_sel, const float* w, const
 // Many rows per sequence (score_many.hip): scores over pooled keys (sb = 1) or
 // the maxima over blocks of sb tokens; row r sees keys below see[r].  The
 // first says which calls it takes.
-bool score_many_takes(const void* k, int kfmt, int n_seq, int rows_per_seq, int n_keys,
+bool score_many_takes(const void* k, int kfmt, int qfmt, int n_seq, int rows_per_seq, int n_keys,
                       bool tokens);
 hipError_t launch_score_many(const void* q, const void* q_scale, int qfmt, const float* w,
                              const void* k, const void* k_scale, int kfmt, int n_seq,

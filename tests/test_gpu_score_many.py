@@ -3,8 +3,8 @@ with the FP64 oracle (needs an MI355X): pooled keys, and per-token keys with
 blocks of 16 and 64 tokens, in every key and query format.
 
 Sizes lie at the edges of its tiles (64 rows and 32 keys per workgroup step,
-runs of several steps) and just past the number of (row, key) pairs that sends
-a call there; what each row sees is random: nothing, everything, past the end,
+runs of several steps) and past the number of (row, key) pairs that sends a call
+there (some quantized ones short of it: the row kernels); what each row sees is random: nothing, everything, past the end,
 and limits inside a tile.  Tolerance as for the row kernels:
 |gpu - oracle| <= 1e-4 |oracle| + 1e-6, the same -inf entries.
 """
@@ -62,7 +62,7 @@ def inputs(n_seq, rows, n_keys, Hs, ds):
 
 @pytest.mark.parametrize("n_seq,rows,n_keys,Hs,ds", [
     (1, 64, 1025, 4, 128), (2, 65, 512, 8, 64), (1, 130, 799, 8, 64), (3, 129, 129, 4, 128),
-    (1, 1030, 63, 4, 128), (40, 17, 97, 8, 64)])
+    (1, 1030, 63, 4, 128), (40, 17, 97, 8, 64), (3, 161, 161, 4, 128), (310, 9, 130, 8, 64)])
 @pytest.mark.parametrize("fmt", FORMATS)
 def test_pooled_keys(n_seq, rows, n_keys, Hs, ds, fmt):
     print(f"[many] pooled {n_seq} x {rows} rows, {n_keys} keys, {Hs}x{ds} {fmt}", flush=True)
@@ -80,7 +80,8 @@ def test_pooled_keys(n_seq, rows, n_keys, Hs, ds, fmt):
 @pytest.mark.parametrize("kfmt", FORMATS)
 def test_pooled_keys_quantized_queries(qfmt, kfmt):
     print(f"[many] pooled q={qfmt} k={kfmt}", flush=True)
-    for n_seq, rows, n_keys, Hs, ds in ((1, 67, 799, 8, 64), (2, 66, 385, 4, 128)):
+    for n_seq, rows, n_keys, Hs, ds in ((1, 67, 799, 8, 64), (2, 66, 385, 4, 128),
+                                        (1, 131, 1001, 8, 64), (2, 130, 513, 4, 128)):
         q, w, k, see = inputs(n_seq, rows, n_keys, Hs, ds)
         qc, qs, qd, qsd = coded(q, qfmt)
         kc, ks, kd, ksd = coded(k, kfmt)
@@ -95,7 +96,7 @@ def test_pooled_keys_quantized_queries(qfmt, kfmt):
 def test_pooled_keys_scales_beyond_their_product():
     """Key and query scales whose product is no FP32 number while every scaled
     sum is one: 2^117 and 2^-126 against FP16 query scales of 2048 and 2^-14."""
-    rows, n_keys, Hs, ds = 96, 1024, 4, 128
+    rows, n_keys, Hs, ds = 128, 1024, 4, 128
     print("[many] pooled extreme scales", flush=True)
     q = np.zeros((rows, Hs, ds), np.int8)
     q[..., ::32] = 1
