@@ -107,10 +107,11 @@ const char *spot_version(void);
  *
  * Supported: h_s * d_s == 512 with d_s in {64, 128}; rope_dim even, 0 <=
  * rope_dim <= d_s; rope_base > 0.  The arithmetic is FP32 (products of
- * BF16, summed in an order that depends on the sizes only; more than 32 rows
- * run on the matrix cores); the rotation angle (position times the
- * pair's frequency rope_base^(-2i/rope_dim), both in FP64) is reduced modulo
- * 2 pi in FP64, its sine and cosine taken in FP32.  Errors:
+ * BF16, summed in an order that depends on the sizes only; more than 32 rows,
+ * or 48 where d_model exceeds 8192, run on the matrix cores); the rotation
+ * angle (position times the pair's frequency rope_base^(-2i/rope_dim), both in
+ * FP64) is reduced modulo 2 pi in FP64, its sine and cosine taken in FP32.
+ * Errors:
  * SPOT_ERR_NULL, SPOT_ERR_SHAPE (sizes, rows % rows_per_seq, alignment),
  * SPOT_ERR_UNSUPPORTED (head shape, rope_dim, rope_base).
  */
@@ -122,7 +123,8 @@ spot_status spot_selector_project(const void *h, const void *w_q, const void *w_
 
 /*
  * spot_selector_project_pooled -- one decode step's selector front end in a
- * single launch (more than 32 sequences: two): spot_selector_project with one row per sequence
+ * single launch (two where spot_selector_project runs on the matrix cores):
+ * spot_selector_project with one row per sequence
  * (rows = n_seq, rows_per_seq = 1), then spot_selector_pool of the block the
  * new key landed in (first_block = pos / 64, max_blocks = 1), with the same
  * arithmetic and summation order, so q_out, w_out, k_cache and k_pool are

@@ -492,9 +492,11 @@ __global__ __launch_bounds__(64 * kSkWaves) void proj_skinny_kernel(ProjectArgs 
 
 bool project_mfma_takes(int rows, int d_model) {
   // Up to two 16-row passes of the row kernel are as fast (13.8 against
-  // 14.1 us for 32 rows of 4096); tile offsets are 32-bit (512 rows of
-  // d_model BF16).
-  return rows > 32 && d_model <= 1 << 21;
+  // 14.1 us for 32 rows of 4096), three where d_model is large (33 / 48 rows of
+  // 8192 25.4 / 27.5 against 25.3, of 16384 40 / 42 against 46, of 32768 69 / 74
+  // against 87; 64 rows of 32768 96 against 87); tile offsets are 32-bit (512 rows
+  // of d_model BF16).
+  return rows > (d_model <= 8192 ? 32 : 48) && d_model <= 1 << 21;
 }
 
 // Which kernel: the skinny one while its grid is at most one workgroup per

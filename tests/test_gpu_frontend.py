@@ -124,6 +124,8 @@ MANY_ROWS = [
     (2049, 512, 4, 128, 64, 2049, 2112),
     (4097, 136, 8, 64, 6, 4097, 4160),
     (4352, 456, 4, 128, 64, 4352, 4352),
+    (48, 8200, 4, 128, 64, 48, 64),      # large d_model: the row kernel up to 48 rows
+    (49, 8200, 8, 64, 32, 49, 64),
 ]
 
 
