@@ -624,16 +624,19 @@ hipError_t launch_select_blocks(const float* scores, int rows, int nblk, const i
   const int spl_wg = top_p >= 1.f && spl > 8 ? 8 : spl;
   // Rows of 65 .. 512 blocks: four waves per row while the rows leave the
   // chip's wave slots idle, one wave per row (less work in all) beyond that.
-  // us, one wave / four, replayed calls (rows x blocks, cap): 4 x 256, 32
-  // 5.6 / 4.8; 8 x 512, 64 6.9 / 5.3; 256 x 256, 64 5.9 / 5.4; 512 x 512, 64
-  // 7.3 / 6.0; 512 x 512, 96 8.2 / 7.6; 1024 x 256, 64 6.3 / 7.0; 2048 x 512,
+  // us, one wave / four, replayed calls (rows x blocks, k_max): 4 x 256, 32
+  // 6.1 / 5.0; 4 x 512, 64 7.2 / 5.7; 256 x 256, 64 6.3 / 5.8; 512 x 512, 64
+  // 7.9 / 6.5; 512 x 512, 100 8.8 / 8.1; 1024 x 256, 64 6.3 / 7.0; 2048 x 512,
   // 64 8.8 / 10.8; 2048 x 512, 200 13.0 / 18.6.  Caps above 128, whose sort
   // is one wave's either way, stay there too, as do rows of at most 64 blocks
-  // (64 rows: 5.1 / 5.1).  With top_p >= 1 only the one wave sorts: 512 x 300,
-  // 64 7.2 / 4.8; 2048 x 512, 512 18.0 / 5.9; so any cap goes (no survivor
-  // buffer), and large caps at any number of rows.
+  // (64 rows: 5.1 / 5.1), and of at most 128 with a cap above 64, which is the
+  // row or nearly so (128 x 80, 100 5.1 / 5.8; 512 x 128, 131 5.3 / 6.1; 512 x
+  // 128, 100 7.0 / 7.3).  With top_p >= 1 only the one wave sorts: 512 x 320, 64
+  // 7.6 / 5.3; 2048 x 512, 512 18.0 / 5.9; so any cap goes (no survivor buffer),
+  // and large caps at any number of rows.
   const bool short_row = nblk > 64 && nblk <= 512, top_k = top_p >= 1.f;
-  const bool short_wg = short_row && (rows <= 512 ? top_k || spl <= 2 : top_k && spl > 2);
+  const bool few = rows <= 512 && (top_k || spl == 1 || (spl == 2 && nblk > 128));
+  const bool short_wg = short_row && (few || (top_k && spl > 2));
   const int spl_short = top_k ? 1 : spl;
   if (short_wg || (nblk > 512 && nblk <= 8192 && spl_wg <= 16)) {
     const int e2 = nblk <= 256 ? 1 : nblk <= 512 ? 2 : nblk <= 1024 ? 4 : nblk <= 2048 ? 8 : nblk <= 4096 ? 16 : 32;
