@@ -73,6 +73,7 @@ def build_binding() -> str:
            "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1", "-I", INCLUDE,
            "-isystem", os.path.join(root, "include"), "-isystem", os.path.join(rocm, "include"),
            "-isystem", sysconfig.get_paths()["include"], "-Wall",
+           f'-DSPOT_TORCH="{torch.__version__}"',
            os.path.join(CSRC, "binding.cpp"), "-o", tmp, "-L", os.path.join(root, "lib"),
            "-ltorch_python", "-ltorch_cpu", "-ltorch", "-lc10", "-lc10_hip",
            f"-Wl,-rpath,{os.path.join(root, 'lib')}"]
@@ -81,6 +82,16 @@ def build_binding() -> str:
         raise RuntimeError(f"g++ failed for binding.cpp:\n{r.stderr}")
     os.replace(tmp, BINDING)
     return BINDING
+
+
+def binding_fits() -> bool:
+    """Whether a marshalling module is there and was built against this torch (whose
+    tensor layout it relies on; another torch's may well import)."""
+    import torch
+    if not os.path.exists(BINDING):
+        return False
+    with open(BINDING, "rb") as f:
+        return f"spot binding for torch {torch.__version__}\0".encode() in f.read()
 
 
 def build(verbose: bool = False) -> str:
@@ -101,9 +112,9 @@ def build(verbose: bool = False) -> str:
 
 
 def stale() -> bool:
-    if not os.path.exists(SO) or not os.path.exists(BINDING):
+    if not os.path.exists(SO):
         return True
-    t = min(os.path.getmtime(SO), os.path.getmtime(BINDING))
+    t = min(os.path.getmtime(f) for f in (SO, BINDING) if os.path.exists(f))
     deps = [os.path.join(CSRC, f) for f in os.listdir(CSRC)] + [os.path.join(INCLUDE, "spot.h")]
     return any(os.path.getmtime(p) > t for p in deps)
 

@@ -26,6 +26,9 @@
 
 namespace {
 
+// Read from the file before it is imported (build.py, binding_fits).
+__attribute__((used)) const char kBuiltFor[] = "spot binding for torch " SPOT_TORCH;
+
 // Entry points of the loaded libspot, in the order spot.py passes them.
 enum Fn {
   kScore, kScoreQ, kScoreTokensBlk, kProject, kProjectPooled, kPool, kSelect, kSparseBlk, kDense,

@@ -119,18 +119,25 @@ def load(path: Optional[str] = None):
 
 
 def _load_native(L):
-    """Hands the library's entry points to the native marshalling module."""
+    """Hands the library's entry points to the native marshalling module.  Where
+    there is none for this torch and none can be built (no compiler or headers),
+    every call takes the Python path, which does all of it, more slowly."""
     global _native
-    if not os.path.exists(_build.BINDING):
-        _build.build_binding()
-    from . import _binding
-    order = (L.spot_selector_score, L.spot_selector_score_q, L.spot_selector_score_tokens_blk,
-             L.spot_selector_project, L.spot_selector_project_pooled, L.spot_selector_pool,
-             L.spot_select_blocks, L.spot_sparse_decode_blk, L.spot_dense_decode,
-             L.spot_sparse_prefill, L.spot_decode_step, L.spot_decode_step_q,
-             L.spot_decode_step_static)
-    _binding.init(tuple(ctypes.cast(f, ctypes.c_void_p).value for f in order), torch.cuda.Stream)
-    _native = _binding
+    try:
+        if not _build.binding_fits():
+            _build.build_binding()
+        from . import _binding
+        order = (L.spot_selector_score, L.spot_selector_score_q, L.spot_selector_score_tokens_blk,
+                 L.spot_selector_project, L.spot_selector_project_pooled, L.spot_selector_pool,
+                 L.spot_select_blocks, L.spot_sparse_decode_blk, L.spot_dense_decode,
+                 L.spot_sparse_prefill, L.spot_decode_step, L.spot_decode_step_q,
+                 L.spot_decode_step_static)
+        _binding.init(tuple(ctypes.cast(f, ctypes.c_void_p).value for f in order),
+                      torch.cuda.Stream)
+        _native = _binding
+    except (ImportError, OSError, RuntimeError) as e:
+        print(f"warning: calls are marshalled in Python (10 us more each): {e}",
+              file=sys.stderr)
 
 
 # ------------------------------------------------------------- marshalling

@@ -4,7 +4,9 @@ bit, and whatever it does not take is left to the Python path (it answers
 None), so that the same calls raise the same errors either way.
 """
 import math
+import shutil
 
+import numpy as np
 import pytest
 import torch
 
@@ -26,6 +28,49 @@ def test_native_leaves_the_rest_to_python():
         f = getattr(spot._native, name)
         for args in ((), (None,) * 40, (cpu,) * 20, (1,) * 20, ("bf16",) * 20, (2 ** 70,) * 20):
             assert f(*args) is None, (name, args)
+
+
+def test_without_the_native_module(monkeypatch, capsys, tmp_path):
+    """No marshalling module and no way to build one: the library still loads, and
+    every call takes the Python path."""
+    if not build.os.path.exists(build.SO):
+        build.build()
+
+    def no_compiler():
+        raise RuntimeError("g++ failed for binding.cpp")
+
+    monkeypatch.setattr(build, "BINDING", str(tmp_path / "_binding.so"))
+    monkeypatch.setattr(build, "build_binding", no_compiler)
+    monkeypatch.setattr(spot, "_lib", None)
+    monkeypatch.setattr(spot, "_native", None)
+    lib = spot.load()
+    assert lib is spot._lib and spot._native is None
+    assert "marshalled in Python" in capsys.readouterr().err
+    with pytest.raises(ValueError, match="scores must be a device tensor"):
+        x = torch.zeros(4)
+        spot.spot_select_blocks(x, 1, 4, None, 0.9, 4, 0, 1, 1, x, x)
+
+
+def test_module_of_another_torch_is_rebuilt(monkeypatch, tmp_path):
+    """The torch it was built against is read from the file before it is imported."""
+    if not build.os.path.exists(build.SO):
+        build.build()
+    if not build.binding_fits():
+        build.build_binding()
+    assert build.binding_fits()
+    other = tmp_path / "_binding.so"
+    shutil.copy(build.BINDING, other)
+    tag = f"spot binding for torch {torch.__version__}".encode()
+    data = other.read_bytes()
+    assert tag in data
+    other.write_bytes(data.replace(tag, tag[:-1] + b"?"))
+    built = []
+    monkeypatch.setattr(build, "BINDING", str(other))
+    monkeypatch.setattr(build, "build_binding", lambda: built.append(1))
+    monkeypatch.setattr(spot, "_lib", None)
+    monkeypatch.setattr(spot, "_native", None)
+    spot.load()
+    assert built == [1]
 
 
 def bf(*shape):
