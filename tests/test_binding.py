@@ -157,13 +157,29 @@ def calls():
     ]
 
 
+class Answers:
+    """The native module, noting what each entry answered."""
+
+    def __init__(self, module):
+        self.module, self.seen = module, []
+
+    def __getattr__(self, name):
+        f = getattr(self.module, name)
+
+        def call(*args):
+            st = f(*args)
+            self.seen.append((name, st))
+            return st
+        return call
+
+
 def both(f, args, kw, monkeypatch):
-    """What the call does with the native module and without: outputs or the error."""
-    seen = []
-    for native in (True, False):
+    """What the call does with the native module and without: outputs or the
+    error; and what the native entry answered."""
+    seen, native = [], Answers(spot._native)
+    for module in (native, None):
         with monkeypatch.context() as m:
-            if not native:
-                m.setattr(spot, "_native", None)
+            m.setattr(spot, "_native", module)
             a = [x.clone() if isinstance(x, torch.Tensor) and x.is_contiguous() and
                  x.data_ptr() % 16 == 0 else x for x in args]
             try:
@@ -172,16 +188,29 @@ def both(f, args, kw, monkeypatch):
                 seen.append(a)
             except Exception as e:       # compared below
                 seen.append((type(e), str(e)))
-    return seen
+    assert len(native.seen) == 1         # every call asks it once
+    return (*seen, native.seen[0][1])
+
+
+def same(nat, py, outs, at):
+    """Equal errors, or equal outputs bit for bit."""
+    if isinstance(nat, tuple) or isinstance(py, tuple):
+        assert nat == py, (*at, nat, py)
+        return
+    for j in outs:
+        if py[j] is not None:
+            assert torch.equal(nat[j].view(torch.uint8), py[j].view(torch.uint8)), (*at, j)
 
 
 @pytest.mark.gpu
 @pytest.mark.skipif(not torch.cuda.is_available(), reason="needs a GPU")
 def test_native_equals_python(monkeypatch):
-    """Every call, on the current stream and on a given one; then every
-    tensor argument in turn made unacceptable (other type, one element short,
-    not contiguous, misaligned, on the host, None) and every positive size negative:
-    the same outputs or the same error."""
+    """Every call, on the current stream and on a given one, is taken by the native
+    entry (a raw stream handle is not) and gives the same outputs, bit for bit.
+    Then every tensor argument in turn made unacceptable or optional (other type, one
+    element short, not contiguous, misaligned, on the host, None) or larger, and
+    every positive size changed (negative, zero, one off, past 32 bits, another
+    kind of number): the same outputs or the same error."""
     torch.manual_seed(3)
     spot.load()
     side = torch.cuda.Stream()
@@ -189,23 +218,26 @@ def test_native_equals_python(monkeypatch):
         print(f"[binding] {f.__name__}", flush=True)
         for stream in (None, side, side.cuda_stream):
             torch.cuda.synchronize()
-            nat, py = both(f, args, dict(kw, stream=stream), monkeypatch)
-            for j in outs:
-                assert torch.equal(nat[j].view(torch.uint8), py[j].view(torch.uint8)), (f, j)
+            nat, py, st = both(f, args, dict(kw, stream=stream), monkeypatch)
+            assert isinstance(nat, list) and isinstance(py, list), (f, nat, py)
+            same(nat, py, outs, (f.__name__, stream))
+            assert st == (None if isinstance(stream, int) else spot.SPOT_OK), (f.__name__, stream)
         for j, x in enumerate(args):
             if isinstance(x, torch.Tensor) and x.numel() > 1:
                 flat = x.reshape(-1)
                 bad = [x.double(), flat[:-1], torch.stack((flat, flat), 1)[:, 0],
-                       torch.cat((flat, flat))[1:1 + flat.numel()], x.cpu(), None]
+                       torch.cat((flat, flat))[1:1 + flat.numel()], x.cpu(), None,
+                       torch.cat((flat, flat))]
                 if x.dtype == torch.uint8 and j == len(args) - 1:
                     bad = [flat[:16], x.cpu(), None]          # a workspace: any type
             elif isinstance(x, int) and x > 0:
-                bad = [-1]
+                bad = [-1, 0, x - 1, x + 1, 2 ** 31, x + 2 ** 32, float(x), np.int64(x), True]
             else:
                 continue
             for b in bad:
-                nat, py = both(f, args[:j] + [b] + args[j + 1:], kw, monkeypatch)
-                if isinstance(py, tuple):
-                    assert nat == py, (f.__name__, j, nat, py)
-                else:
-                    assert isinstance(nat, list), (f.__name__, j, nat)
+                at = (f.__name__, j, tuple(b.shape) if isinstance(b, torch.Tensor) else b)
+                nat, py, st = both(f, args[:j] + [b] + args[j + 1:], kw, monkeypatch)
+                same(nat, py, outs, at)
+                if isinstance(b, torch.Tensor) and b.is_cuda and b.dtype == x.dtype and \
+                        b.numel() == 2 * x.numel():
+                    assert st == spot.SPOT_OK, at             # slack is no reason to decline
