@@ -119,7 +119,8 @@ def test_selector_score_ragged():
 
 
 def test_selector_score_prefill_rows():
-    """rows_per_seq > 1: query-block x key-block scores with a causal n_valid."""
+    """rows_per_seq > 1: query-block x key-block scores with a causal n_valid
+    (64 blocks: the row kernel)."""
     wl = synth.prefill_config(L=4096, backbone=False)
     nqb = wl.nblk
     s_o = oracle.selector_score(wl.q_sel, wl.w, wl.k_sel, rows_per_seq=nqb, n_valid=wl.n_valid)
@@ -128,12 +129,13 @@ def test_selector_score_prefill_rows():
     assert_scores_close(s_g.cpu().numpy(), s_o)
 
 
-@pytest.mark.parametrize("B,nqb,Hs,ds", [(2, 48, 8, 64), (3, 32, 4, 128), (1, 20, 8, 64)])
+@pytest.mark.parametrize("B,nqb,Hs,ds", [(2, 48, 8, 64), (3, 32, 4, 128), (1, 20, 8, 64),
+                                         (2, 176, 8, 64), (1, 260, 4, 128), (5, 129, 4, 128)])
 def test_selector_score_prefill_tiles(B, nqb, Hs, ds):
-    """Query-block x key-block scores on the matrix cores (rows_per_seq a
-    multiple of 16) and on the row kernel otherwise: several sequences,
-    a block count that is not a multiple of the 32-block workgroup tile,
-    both head splits of the 512-wide pooled key, a causal n_valid."""
+    """Query-block x key-block scores of a prompt, on the row kernel (the first
+    three: few blocks) and on the matrix cores: several sequences, block counts
+    that are no multiple of its tiles (64 rows, 32 keys a step), both head
+    splits of the 512-wide pooled key, a causal n_valid."""
     rng = np.random.default_rng([B, nqb, Hs, ds])
     q_sel, w, k_sel = synth.selector_prefill(rng, B, nqb, nqb, Hs, ds)
     q_sel = q_sel.reshape(B * nqb, Hs, ds)
