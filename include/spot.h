@@ -110,7 +110,9 @@ const char *spot_version(void);
  * BF16, summed in an order that depends on the sizes only; more than 32 rows,
  * or 48 where d_model exceeds 8192, run on the matrix cores); the rotation
  * angle (position times the pair's frequency rope_base^(-2i/rope_dim), both in
- * FP64) is reduced modulo 2 pi in FP64, its sine and cosine taken in FP32.
+ * FP64) is reduced modulo pi/2 in FP64, its sine and cosine taken in FP32 to
+ * within 1e-7 for angles up to 2^40 (a rope_base below 1 can give larger ones: from
+ * 2^53 on they are only bounded).
  * Errors:
  * SPOT_ERR_NULL, SPOT_ERR_SHAPE (sizes, rows % rows_per_seq, alignment),
  * SPOT_ERR_UNSUPPORTED (head shape, rope_dim, rope_base).

@@ -15,16 +15,20 @@ struct RopeFreq {
 
 // Sine and cosine of pos * freq: the angle in FP64, reduced in FP64 by a
 // multiple of pi/2 (in two parts) to [-pi/4, pi/4], then the minimax
-// polynomials of Moshier's Cephes library for that range in FP32 (errors
-// below 1e-7; a general sincosf brings its own reduction for large arguments
-// along, three times the instructions).
-__device__ __forceinline__ void rope_sincos(int pos, double freq, float& s, float& c) {
+// polynomials of Moshier's Cephes library for that range in FP32 (a general
+// sincosf brings its own reduction for large arguments along, three times the
+// instructions).  Errors against the sine and cosine of the FP64 angle are below
+// 1e-7 for angles up to 2^40; past 2^53, which only a rope_base below 1 gives,
+// the quarter turns are no longer exact, and the clamp keeps the values bounded
+// (the angle itself, rounded to FP64, has no fraction of a turn left there).
+// (On the host for its test.)
+__host__ __device__ __forceinline__ void rope_sincos(int pos, double freq, float& s, float& c) {
   const double theta = (double)pos * freq;
   const double k = rint(theta * 0.6366197723675814);    // 2 / pi
   double red = fma(-k, 1.5707963267948966, theta);      // pi / 2, high part
   red = fma(-k, 6.123233995736766e-17, red);            // pi / 2, low part
   const int q = (int)(k - 4.0 * floor(k * 0.25));       // quarter turns, 0 .. 3
-  const float x = (float)red, z = x * x;
+  const float x = fminf(fmaxf((float)red, -0.79f), 0.79f), z = x * x;
   const float sn =
       fmaf(fmaf(fmaf(-1.9515295891e-4f, z, 8.3321608736e-3f), z, -1.6666654611e-1f) * z, x, x);
   const float cs = fmaf(

@@ -79,6 +79,7 @@ CASES = [
     (20, 2560, 4, 128, 64, 1.0e4, 20, 64),       # prefill rows, two row passes
     (6, 1000, 8, 64, 64, 500.0, 3, 128),         # d_model not a multiple of 512, all dims rotated
     (2, 512, 4, 128, 0, 1.0e6, 1, 64),           # no rotary dims
+    (7, 264, 4, 128, 64, 2.0 ** -10, 1, 4096),   # a base below 1 (an FP32 number): angles to 4e6
 ]
 
 
@@ -192,6 +193,30 @@ def test_project_many_rows_infinities(rows):
     w = got[0].cpu().numpy()
     assert np.all(w[1:4] == np.inf) and np.all(w[4] == -np.inf) and np.all(np.isnan(w[5]))
     assert np.all(np.isfinite(np.delete(w, [1, 2, 3, 4, 5, rows - 1], 0)))
+
+
+@pytest.mark.parametrize("rows", [5, 70])
+def test_rotation_stays_bounded(rows):
+    """Angles past 2^53 (a rope_base far below 1) carry no phase, but sine and
+    cosine stay within [-1, 1]: a rotated pair is at most as long as twice the pair."""
+    d_model, Hs, ds, l_cap = 256, 4, 128, 1 << 20
+    h, wq, wk, ww = synth.selector_frontend(9, rows, d_model, Hs, ds)
+    W = [bf(x) for x in (wq, wk, ww)]
+    pos = dev((l_cap - 1 - 1000 * np.arange(rows)).astype(np.int32))
+    got = []
+    for rope in (64, 0):
+        q_out = torch.empty((rows, Hs, ds), dtype=torch.bfloat16, device=DEV)
+        w_out = torch.empty((rows, Hs), dtype=torch.float32, device=DEV)
+        cache = torch.empty(Hs * ds, dtype=torch.bfloat16, device=DEV)
+        spot.spot_selector_project(bf(h), *W, pos, rows, d_model, Hs, ds, rope, 1.0e-30, q_out,
+                                   w_out, cache, rows, 0)            # (no key is stored)
+        torch.cuda.synchronize()
+        got.append(q_out.float().cpu().numpy())
+    rot, plain = got
+    assert np.all(np.isfinite(rot))
+    pair = np.hypot(plain[..., :32], plain[..., 32:64])
+    assert np.all(np.hypot(rot[..., :32], rot[..., 32:64]) <= 2.0 * pair + 1e-6)
+    assert np.array_equal(rot[..., 64:], plain[..., 64:])
 
 
 def test_project_skips_keys_outside_the_cache():
