@@ -100,21 +100,21 @@ __global__ __launch_bounds__(kProjWaves * 64) void project_kernel(
     const int32_t* __restrict__ pos, int rows, int d_model, int h_s, int d_s, int rope_dim,
     RopeFreq freq, uint16_t* __restrict__ q_out, float* __restrict__ w_out,
     uint16_t* __restrict__ k_cache, int rows_per_seq, int l_cap,
-    uint16_t* __restrict__ k_pool, const int32_t* __restrict__ seq_len, int row_base) {
+    uint16_t* __restrict__ k_pool, const int32_t* __restrict__ seq_len) {
   static_assert(RP >= kProjWaves && (RP & (RP - 1)) == 0, "RP: a power of two >= the waves");
   __shared__ float part[kProjWaves][RP][4];   // [wave][row][row a, b, W_w c, d]
   __shared__ float pool_new[POOL ? RP : 1][2];   // the new key's value, [row][dim a/b]
   constexpr int kRows = POOL ? RP / kProjWaves : 1;   // rows gathered per wave
   constexpr int kPass = kProjWaves * 512 * CH;        // d elements per pass
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  // Row pass blockIdx.y (RP rows from row_base + RP * blockIdx.y).
+  // Row pass blockIdx.y (RP rows from RP * blockIdx.y).
   // 1. every lane: position and length (the position again without
   // seq_len) of row r0 + lane % RP (the last row for lanes past the end),
   // the first loads; lane r of wave 0 finishes row r0 + r, wave w gathers
   // rows r0 + w + 4m.  Every load is unconditional (addresses clamped into
   // their buffers, unused values masked where they are used), so that no
   // branch join makes a wave wait for a load before it issues the next ones.
-  const int r0 = row_base + (int)blockIdx.y * RP;
+  const int r0 = (int)blockIdx.y * RP;
   const int nr = min(RP, rows - r0);
   const int lr = r0 + min(lane & (RP - 1), nr - 1);
   const int pos_l = pos[lr];
@@ -403,37 +403,26 @@ hipError_t launch_selector_project(const void* h, const void* w_q, const void* w
     return (reinterpret_cast<uintptr_t>(k_cache) & 15u) == 0 ? pool(pool_kernel<true>)
                                                              : pool(pool_kernel<false>);
   }
+  // One row pass per workgroup row (at most 3; above the tile kernels' d_model
+  // as many rows as memory holds, a few thousand passes).
   const int rp = rows <= 4 ? 4 : (rows <= 8 ? 8 : 16);
-  const int passes = (rows + rp - 1) / rp;
-  // one row pass per workgroup row; more than 65535 passes take more launches
-  for (int p0 = 0; p0 < passes; p0 += 65535) {
-    const dim3 grid(tasks, passes - p0 < 65535 ? passes - p0 : 65535);
-    auto go = [&](auto kern) {
-      hipLaunchKernelGGL(kern, grid, dim3(kProjWaves * 64), 0, s,
-                         static_cast<const uint16_t*>(h), static_cast<const uint16_t*>(w_q),
-                         static_cast<const uint16_t*>(w_k), static_cast<const uint16_t*>(w_w),
-                         pos, rows, d_model, h_s, d_s, rope_dim, freq,
-                         static_cast<uint16_t*>(q_out), w_out, static_cast<uint16_t*>(k_cache),
-                         rows_per_seq, l_cap, static_cast<uint16_t*>(k_pool), seq_len, p0 * rp);
-    };
-    if (k_pool) {   // one row per sequence (the caller checks rows_per_seq == 1)
-      if (rp == 4)
-        go(project_kernel<4, 2, true>);
-      else if (rp == 8)
-        go(project_kernel<8, 2, true>);
-      else
-        go(project_kernel<16, 1, true>);
-    } else if (rp == 4) {
-      go(project_kernel<4, 2, false>);
-    } else if (rp == 8) {
-      go(project_kernel<8, 2, false>);
-    } else {
-      go(project_kernel<16, 1, false>);
-    }
-    const hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-  }
-  return hipGetLastError();
+  const dim3 grid(tasks, (rows + rp - 1) / rp);
+  auto go = [&](auto kern) {
+    hipLaunchKernelGGL(kern, grid, dim3(kProjWaves * 64), 0, s,
+                       static_cast<const uint16_t*>(h), static_cast<const uint16_t*>(w_q),
+                       static_cast<const uint16_t*>(w_k), static_cast<const uint16_t*>(w_w),
+                       pos, rows, d_model, h_s, d_s, rope_dim, freq,
+                       static_cast<uint16_t*>(q_out), w_out, static_cast<uint16_t*>(k_cache),
+                       rows_per_seq, l_cap, static_cast<uint16_t*>(k_pool), seq_len);
+    return hipGetLastError();
+  };
+  if (k_pool)   // one row per sequence (the caller checks rows_per_seq == 1)
+    return rp == 4   ? go(project_kernel<4, 2, true>)
+           : rp == 8 ? go(project_kernel<8, 2, true>)
+                     : go(project_kernel<16, 1, true>);
+  return rp == 4   ? go(project_kernel<4, 2, false>)
+         : rp == 8 ? go(project_kernel<8, 2, false>)
+                   : go(project_kernel<16, 1, false>);
 }
 
 hipError_t launch_selector_pool(const void* k_tok, void* k_pool, int n_seq, int l_cap,
