@@ -272,12 +272,12 @@ __global__ __launch_bounds__(256, 2) void score_many_kernel(ManyArgs a) {
             const int g = h * KS + x;
             const u32x4 kf = *reinterpret_cast<const u32x4*>(kr + swz(r16, g * 4 + kg) * 16);
             if constexpr (SCALED) {
-              // (one scale after the other: their product may overflow where
-              // the scaled sum does not)
+              // (the query's FP16 scale first: neither the product of the scales nor
+              // a sum under the key's alone need be an FP32 number)
               e[x] = mfma(kf, qf[g], f32x4{0.f, 0.f, 0.f, 0.f});
+              if constexpr (QINT) e[x] *= qs[g];
               if constexpr (KQ)
                 e[x] *= *reinterpret_cast<const f32x4*>(sc + g * kKeys + 16 * t + 4 * kg);
-              if constexpr (QINT) e[x] *= qs[g];
             } else {
               e[x] = mfma(kf, qf[g], x & 1 ? e[x - 1] : f32x4{0.f, 0.f, 0.f, 0.f});
             }
@@ -431,9 +431,10 @@ bool score_many_takes(const void* k, int kfmt, int qfmt, int n_seq, int rows_per
                  : rows_per_seq >= 4 && pairs >= (keys >= 8192. ? 65536. : 98304.);
   const bool four_bit = kfmt == SPOT_KFMT_INT4_G32 || kfmt == SPOT_KFMT_MXFP4_G32;
   const double rounds = (double)((p.wgs + 511) / 512);
+  const bool qint = qfmt == SPOT_KFMT_INT4_G32 || qfmt == SPOT_KFMT_INT8_G32;
   double here = p.wgs <= 256 && p.steps == 1 ? (quant ? 5.7 : 5.1)
-                : rounds * (quant ? 3.8 + 3.0 * p.steps : 2.9 + 2.9 * p.steps);
-  if (qfmt == SPOT_KFMT_INT4_G32 || qfmt == SPOT_KFMT_INT8_G32)
+                : rounds * (quant ? 3.8 + (qint ? 3.6 : 3.0) * p.steps : 2.9 + 2.9 * p.steps);
+  if (qint)
     here += 3.9;
   else if (qfmt != SPOT_KFMT_BF16)
     here += 2.3;

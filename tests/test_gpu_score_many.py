@@ -93,33 +93,40 @@ def test_pooled_keys_quantized_queries(qfmt, kfmt):
         assert_scores_close(out.cpu().numpy(), s_o)
 
 
-def test_pooled_keys_scales_beyond_their_product():
-    """Key and query scales whose product is no FP32 number while every scaled
-    sum is one: 2^117 and 2^-126 against FP16 query scales of 2048 and 2^-14."""
+def test_pooled_keys_extreme_scales():
+    """Key and query scales whose product is no FP32 number (2^117 and 2^-126
+    against 2048 and 2^-14), and sums that are none under the key's scale alone
+    (32 x 127 x 448 x 2^108, times 2^-10): every score is one, and exact."""
     rows, n_keys, Hs, ds = 128, 1024, 4, 128
     print("[many] pooled extreme scales", flush=True)
-    q = np.zeros((rows, Hs, ds), np.int8)
-    q[..., ::32] = 1
-    qs = np.full((rows, Hs, 4), 2048.0, np.float16)
-    qs[1::2] = 2.0 ** -14
-    kc = np.zeros((1, n_keys, Hs, ds), np.uint8)
-    kc[..., ::32] = 0x01                       # E4M3 2^-9
-    ks = np.full((1, n_keys, Hs, 4), 127 + 117, np.uint8)
-    kc[:, 1::2, :, ::32] = 0x78                # E4M3 2^8
-    ks[:, 1::2] = 127 - 126
-    w = np.ones((rows, Hs), np.float32)
-    got = []
-    for n in (rows, 4):                        # all rows, or four a call (the row kernel)
-        for at in range(0, rows, n):
-            out = torch.zeros((n, n_keys), device=DEV)
-            spot.spot_selector_score_q(dev(q[at:at + n]), dev(qs[at:at + n].view(np.int16)), "int8",
-                                       dev(w[at:at + n]), dev(kc), dev(ks), "mxfp8", 1, n, n_keys,
-                                       Hs, ds, None, out)
-            got.append(out.cpu().numpy())
-    want = 16 * np.where(np.arange(rows) % 2, 2.0 ** -14, 2048.0)[:, None] * \
-        np.where(np.arange(n_keys) % 2, 2.0 ** -118, 2.0 ** 108)
-    for g in (got[0], np.concatenate(got[1:])):
-        assert np.array_equal(g.astype(np.float64), want)
+    # (query code, scale, key code, scale, elements of a group that are not zero)
+    for qv, kv, nz in ((((1, 2048.0), (1, 2.0 ** -14)), ((0x01, 117, 2.0 ** -9), (0x78, -126, 256.0)),
+                        1),
+                       (((127, 2.0 ** -10), (-127, 2.0 ** -10)), ((0x7E, 108, 448.0),
+                                                                (0x7E, 107, 448.0)), 32)):
+        q = np.zeros((rows, Hs, 4, 32), np.int8)
+        qs = np.zeros((rows, Hs, 4), np.float16)
+        kc = np.zeros((1, n_keys, Hs, 4, 32), np.uint8)
+        ks = np.zeros((1, n_keys, Hs, 4), np.uint8)
+        for i in (0, 1):                       # even and odd rows and keys
+            q[i::2, ..., :nz] = qv[i][0]
+            qs[i::2] = qv[i][1]
+            kc[:, i::2, ..., :nz] = kv[i][0]
+            ks[:, i::2] = 127 + kv[i][1]
+        w = np.ones((rows, Hs), np.float32)
+        got = []
+        for n in (rows, 4):                    # all rows, or four a call (the row kernel)
+            for at in range(0, rows, n):
+                out = torch.zeros((n, n_keys), device=DEV)
+                spot.spot_selector_score_q(dev(q[at:at + n]), dev(qs[at:at + n].view(np.int16)),
+                                           "int8", dev(w[at:at + n]), dev(kc), dev(ks), "mxfp8", 1,
+                                           n, n_keys, Hs, ds, None, out)
+                got.append(out.cpu().numpy())
+        qval = np.array([v[0] * v[1] for v in qv])[np.arange(rows) % 2]
+        kval = np.array([v[2] * 2.0 ** v[1] for v in kv])[np.arange(n_keys) % 2]
+        want = np.maximum(16.0 * nz * qval[:, None] * kval, 0.0)
+        for g in (got[0], np.concatenate(got[1:])):
+            assert np.array_equal(g.astype(np.float64), want)
 
 
 @pytest.mark.parametrize("n_seq,rows,L,Hs,ds", [
@@ -209,3 +216,39 @@ def test_misaligned_codes(fmt, offset, tokens):
         o = oracle.selector_score(q, w, kc, ks, fmt, rows_per_seq=rows, n_valid=see, nblk=n,
                                   h_s=Hs, d_s=ds)
     assert_scores_close(out.cpu().numpy(), o)
+
+
+@pytest.mark.parametrize("fmt", FORMATS)
+def test_pooled_keys_special_values(fmt):
+    """NaN, infinities and the smallest numbers in w and in BF16 keys and queries:
+    the same scores are NaN, +inf and -inf as from the row kernel, which takes the
+    same rows four at a time."""
+    rows, n, Hs, ds = 132, 1030, 8, 64
+    print(f"[many] pooled special values {fmt}", flush=True)
+    q, w, k, see = inputs(1, rows, n, Hs, ds)
+    w[3, 1] = np.nan
+    w[20:40, 2] = np.nan
+    w[40:50, 0] = np.inf
+    w[50:60, 7] = -np.inf
+    w[60:70] *= 1e-38
+    w[70:80] *= -1
+    q[90, 5, 3], q[91, 6, 60], q[92, 0, 0] = 0x7FC0, 0x7F80, 0x0001
+    if fmt == "bf16":
+        k[0, 100:140, 1, 5] = 0x7FC0
+        k[0, 300:310, 2, 9] = 0xFF80
+        k[0, 700:720] = 0x0001
+    _, _, kd, ksd = coded(k, fmt)
+
+    def run(at, m):
+        return spot.selector_score(bf(q[at:at + m]), dev(w[at:at + m]), kd, ksd, fmt,
+                                   rows_per_seq=m, n_valid=dev(see[at:at + m]),
+                                   nblk=n).cpu().numpy()
+
+    many = run(0, rows)
+    few = np.concatenate([run(at, 4) for at in range(0, rows, 4)])
+    assert np.any(np.isnan(few)) and np.any(few == np.inf)
+    assert np.array_equal(np.isnan(many), np.isnan(few))
+    assert np.array_equal(np.isinf(many) * np.sign(many), np.isinf(few) * np.sign(few),
+                          equal_nan=True)
+    fin = np.isfinite(few)
+    assert np.all(np.abs(many[fin] - few[fin]) <= 1e-4 * np.abs(few[fin]) + 1e-6)
